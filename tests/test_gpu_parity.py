@@ -160,12 +160,43 @@ def test_prefill_is_deterministic_and_output_buffer_reuse():
     assert np.array_equal(bits_of(a), bits_of(b))
 
 
+@pytest.mark.parametrize("d,pattern,window", [(128, 0, 0), (128, 3, 0), (64, 0, 0), (64, 3, 0), (128, 0, 40), (64, 0, 40)])
+def test_prefill_takes_a_large_key_as_reference(d, pattern, window):
+    """Every score is 0 but one key's, beyond the first tile, which is log2(16 / 15 * 2^9) = 9.09 in log2 units: more than the 8
+    by which a key may exceed a row's softmax reference, so it becomes the reference and its own probability is 1.  The
+    other probabilities are then 15 / 16 * 2^-9.  bf16 holds both exactly, so the weights carry no rounding of the
+    probabilities; against a reference that stays a whole number of units from the first tile's maximum, 16 / 15 is 3.4e-3
+    off and a row's two halves, +1 and -1, cancel to less than that."""
+    from workloads import f32_to_bf16_bits
+    f, ph, pw, t, hq, hkv, dom = 3, 15, 21, 900, 2, 1, 150
+    n = f * ph * pw + t
+    q, k, v = (np.zeros((x, n, d), dtype=np.float32) for x in (hq, hkv, hkv))
+    x, parts = math.log2(16.0 / 15.0 * 512.0), []
+    for _ in range(3):   # as a sum of three bf16 numbers
+        parts.append(float(F64(f32_to_bf16_bits(np.array([x], dtype=np.float32)))[0]))
+        x -= parts[-1]
+    q[:, :, :3] = 1.0
+    k[:, dom, :3] = parts
+    v[:] = -1.0
+    v[:, dom] = 1.0
+    q, k, v = f32_to_bf16_bits(q), f32_to_bf16_bits(k), f32_to_bf16_bits(v)
+    plan = pk.Plan(f, ph, pw, t, hq, hkv, d, pattern, math.log(2.0), lse_window=window)
+    lse = torch.zeros((hq, n), dtype=torch.float32, device="cuda")
+    out, _ = pk.purekv_st_spattn_prefill(plan, to_dev(q), to_dev(k), to_dev(v), lse=lse)
+    torch.cuda.synchronize()
+    ref, _ = orc.masked_attention(F64(q), F64(k), F64(v), f, ph * pw, t, pattern, scale=math.log(2.0))
+    assert (np.abs(ref[:, dom:]) < 0.2).any()
+    # the output's own rounding (half a unit of 8 significant bits), and fp32 sums of a thousand terms beside it
+    over = np.abs(f64_of(out) - ref) - (2.0 ** -8 * np.abs(ref) + 5e-5)
+    assert over.max() <= 0.0, f"error {over.max():.3g} over the bound in {(over > 0.0).sum()} elements"
+
+
 @pytest.mark.parametrize("d,step", [(128, 0.75), (128, 12.0), (64, 12.0), (64, -0.75), (128, 300.0)])
 @pytest.mark.parametrize("pattern", [0, 3])
 def test_prefill_reference_is_raised(pattern, d, step):
-    """Scores that grow (or fall) by `step` log2 units every 16 keys: the softmax reference, taken from a row's first key tile,
-    has to be raised never, every few tiles, or by more than a float's exponent range at once (300: the
-    probabilities of a tile overflow before they are formed again), also in the slices of split lists."""
+    """Scores that grow (or fall) by `step` log2 units every 16 keys: the softmax reference has to be raised never, every few
+    tiles, or by more than a float's exponent range at once (300: probabilities against the reference before would
+    overflow), also in the slices of split lists."""
     from workloads import f32_to_bf16_bits
     rng = np.random.default_rng(int(d + 8 * abs(step)))
     f, ph, pw, t, hq, hkv = 3, 9, 11, 470, 2, 1
