@@ -322,17 +322,18 @@ __global__ __launch_bounds__(DEC_NT) void decode_kernel(const DecodeArgs a) {
       };
       load_batch(part);
       float pm = fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0]));
-      pm = group_max<LPR>(pm);   // finite: every chunk holds at least one key
+      pm = group_max<LPR>(pm);
       const float mnew = fmaxf(run_m, pm);
+      const float mref = (mnew == -INFINITY) ? 0.f : mnew;   // every score so far is -inf: weights 0, not NaN
       float lsum = 0.f;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float f = __builtin_amdgcn_exp2f(ml[r][0] - mnew);
+        const float f = __builtin_amdgcn_exp2f(ml[r][0] - mref);
         lsum += ml[r][1] * f;
         wl[li + r * LPR] = f;
       }
       lsum = group_sum<LPR>(lsum);
-      const float fo = __builtin_amdgcn_exp2f(run_m - mnew);   // first pass: 2^(-inf) = 0
+      const float fo = __builtin_amdgcn_exp2f(run_m - mref);   // first pass: 2^(-inf) = 0
       acc *= fo;
       run_l = run_l * fo + lsum;
       run_m = mnew;

@@ -459,6 +459,25 @@ def test_decode_step_merges_many_chunks(hq, hkv, d, n0):
     check_attention(f64_of(outs[0]), orc.decode_attention(F64(q), F64(kc_h), F64(vc_h)), f"decode {hq}/{hkv} d={d} n={n0 + 1}")
 
 
+@pytest.mark.parametrize("hq,hkv,d,n0", [(2, 1, 64, 64 * 256 + 40), (2, 1, 128, 128 * 256 + 40), (2, 1, 64, 700)])
+def test_decode_step_with_scores_of_minus_infinity(hq, hkv, d, n0):
+    """Keys whose scores overflow to -inf have no weight, also where they fill every chunk of the final merge's first pass
+    (64 chunks of 64-wide heads, 128 of 128-wide ones)."""
+    from workloads import f32_to_bf16_bits
+    rng = np.random.default_rng(n0)
+    q, kn, vn = (rng.standard_normal((x, d)).astype(np.float32) for x in (hq, hkv, hkv))
+    kc, vc = (rng.standard_normal((hkv, n0 + 1, d)).astype(np.float32) for _ in range(2))
+    q[:, 0] = 2.0 ** 100
+    kc[:, :, 0], kn[:, 0] = -2.0 ** 100, 0.0
+    kc[:, n0 - 39:, 0] = 0.0
+    q, kn, vn, kc, vc = (f32_to_bf16_bits(x) for x in (q, kn, vn, kc, vc))
+    plan = pk.Plan(1, 4, 4, 4, hq, hkv, d, 3)
+    out = pk.purekv_decode_step(plan, to_dev(q), to_dev(kn), to_dev(vn), to_dev(kc), to_dev(vc), n0)
+    torch.cuda.synchronize()
+    kc[:, n0], vc[:, n0] = kn, vn
+    check_attention(f64_of(out), orc.decode_attention(F64(q), F64(kc), F64(vc)), f"-inf scores d={d} n={n0 + 1}")
+
+
 def test_tiny_config_end_to_end_chain():
     """Config 1: importance from the dense pass, ST-SpAttn prefill, V-norm top-h at ratio 0.2, compaction, one
     decode step -- every stage fed by the GPU's own previous stage and compared with the oracle's chain."""
