@@ -3,17 +3,21 @@
 // A short clip's step is eight small calls and a generated token one call per layer: the GPU needs 3-15 us for each,
 // and marshalling them through Python and ctypes took the host 11-12 us per call (tensor attributes one by one, the
 // stream object, eleven ctypes conversions), so the host, not the GPU, set the time.  Here a call reads its tensors
-// through at::Tensor and asks c10 for the current stream.  The checks and their messages are those of the Python
-// binding; the C ABI's functions are called through pointers handed over by the binding (`bind`), so that whatever
-// library it loaded is the one that runs.  The GIL is released around every C call, as ctypes does.
+// through at::Tensor and asks c10 for the current stream.  A refused tensor raises the type and text that the binding's
+// own checks raise (TypeError; AssertionError for the fp32 and int32 ones, here with a text), an exception of torch's
+// C++ code the type that torch's Python functions raise for it (OutOfMemoryError, IndexError, ...).  The C ABI's functions
+// are called through pointers handed over by the binding (`bind`), so that whatever library it loaded is the one that
+// runs.  The GIL is released around every C call, as ctypes does.
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <sstream>
 #include <string>
@@ -91,6 +95,12 @@ const at::Tensor& dev_bf16(PyObject* o, const char* name) {
   return t;
 }
 
+void print(std::ostream& s, at::IntArrayRef x) {   // as Python prints a tuple
+  s << '(';
+  for (size_t i = 0; i < x.size(); ++i) s << (i ? ", " : "") << x[i];
+  s << (x.size() == 1 ? ",)" : ")");
+}
+
 // A (..., heads, n, d) bf16 device view with the given head and token strides and contiguous channels.
 const at::Tensor& strided_bf16(PyObject* o, const char* name, int64_t heads, int64_t n, int64_t d, const int64_t* st) {
   const at::Tensor& t = tensor(o, name);
@@ -100,8 +110,12 @@ const at::Tensor& strided_bf16(PyObject* o, const char* name, int64_t heads, int
   if (r < 3 || size[r - 3] != heads || size[r - 2] != n || size[r - 1] != d || stride[r - 1] != 1 ||
       stride[r - 3] != st[0] || stride[r - 2] != st[1]) {
     std::ostringstream s;
-    s << name << ": shape " << size << " / strides " << stride << " do not match the plan ((" << heads << ", " << n << ", " << d
-      << "), head stride " << st[0] << ", token stride " << st[1] << ", channel stride 1)";
+    s << name << ": shape ";
+    print(s, size);
+    s << " / strides ";
+    print(s, stride);
+    s << " do not match the plan ((" << heads << ", " << n << ", " << d << "), head stride " << st[0] << ", token stride "
+      << st[1] << ", channel stride 1)";
     raise(PyExc_TypeError, s.str());
   }
   return t;
@@ -310,8 +324,8 @@ PyObject* guarded(F f) {
   try {
     return f();
   } catch (const Raised&) {
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (const std::exception&) {
+    torch::translate_exception_to_python(std::current_exception());
   }
   return nullptr;
 }

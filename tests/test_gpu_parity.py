@@ -843,6 +843,20 @@ def test_two_streams_share_one_plan():
             assert np.array_equal(bits_of(decs[i][rnd]), bits_of(decs[i][0]))
 
 
+def test_an_output_that_does_not_fit_raises_out_of_memory():
+    wl = SMALL["heads3_4f"]
+    inp = generate(wl, seed=3)
+    plan = _plan(wl, 3)
+    k, v = to_dev(inp.k), to_dev(inp.v)
+    idx = torch.arange(40, dtype=torch.int32, device="cuda").repeat(wl.n_kv_heads, 1)
+    cap = 2 ** 31 - 1
+    assert wl.n_kv_heads * cap * wl.head_dim * 2 > torch.cuda.mem_get_info()[1]
+    with pytest.raises(torch.OutOfMemoryError):
+        pk.purekv_kv_compact(plan, k, v, idx, cap=cap)
+    kc, vc = pk.purekv_kv_compact(plan, k, v, idx)
+    assert torch.equal(kc, k[:, :40]) and torch.equal(vc, v[:, :40])
+
+
 def test_two_threads_grow_one_workspace():
     """Two threads on one stream and one plan whose decode calls need larger and larger workspaces: a buffer that one
     thread replaces stays alive until the other's launch is queued.  Bit-equal to the same calls from one thread."""

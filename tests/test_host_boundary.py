@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2510_25600_amd as pk
 from oracle import purekv_oracle as orc
@@ -417,6 +418,47 @@ def test_head_subset_plan_argument_errors():
     assert lib.purekv_plan_destroy(h) == pk.OK
     with pytest.raises(ValueError):
         pk.Plan(2, 4, 4, 8, 4, 2, 64, 3, host_only=True, head_mask=[1, 0])
+
+
+class _Refusing(torch.Tensor):
+    """A bf16 tensor that says it is on the GPU and whose operations raise: what the hot calls do with an exception of
+    torch's code, without a GPU."""
+
+    @staticmethod
+    def __new__(cls, *shape):
+        return torch.Tensor._make_wrapper_subclass(cls, shape, dtype=torch.bfloat16, device="cuda:0")
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise torch.OutOfMemoryError(f"no memory for {func}")
+
+
+def test_hot_calls_raise_the_types_of_torchs_exceptions():
+    plan = pk.Plan(2, 4, 4, 8, 4, 2, 64, 3, host_only=True)
+    n = plan.N
+    q, kc, vc = _Refusing(4, 64), _Refusing(2, 10, 64), _Refusing(2, 10, 64)
+    qs, ks = _Refusing(4, n, 64), _Refusing(2, n, 64)
+    # an output that cannot be allocated
+    with pytest.raises(torch.OutOfMemoryError, match="no memory for aten.empty"):
+        pk.purekv_decode_attn(plan, q, kc, vc, 10)
+    with pytest.raises(torch.OutOfMemoryError, match="no memory for aten.empty"):
+        pk.purekv_decode_step(plan, q, _Refusing(2, 64), _Refusing(2, 64), kc, vc, 9)
+    # a cache of too few dimensions
+    with pytest.raises(IndexError) as e:
+        pk.purekv_decode_attn(plan, q, _Refusing(64), vc, 10)
+    assert "Exception raised from" not in str(e.value)   # (no C++ backtrace)
+    # refused tensors: the texts of the binding's own checks
+    with pytest.raises(TypeError, match="^kc must be a contiguous bf16 device tensor$"):
+        pk.purekv_decode_attn(plan, q, torch.zeros(2, 10, 64, dtype=torch.bfloat16), vc, 10)
+    for bad in (_Refusing(3, n, 64), _Refusing(64)):
+        with pytest.raises(TypeError) as e:
+            pk.purekv_st_spattn_prefill(plan, qs, bad, ks)
+        with pytest.raises(TypeError) as own:
+            pk.binding._strided_bf16(bad, "k", plan.Hkv, n, 64, plan.kv_strides)
+        assert str(e.value) == str(own.value)
+    with pytest.raises(AssertionError):
+        pk.purekv_topk_select(plan, qs, None, 8, 4)
+    plan.close()
 
 
 @pytest.mark.parametrize("mask", [[0, 0, 0, 0, 1, 1, 1, 1], [1] * 8])
