@@ -163,21 +163,26 @@ void check(int status, const char* where) {
   throw Raised{};
 }
 
+Workspace* find_workspace(PlanObject* p, int op, hipStream_t stream) {
+  for (Workspace& x : *p->ws)
+    if (x.op == op && x.stream == stream) return &x;
+  return nullptr;
+}
+
 // The plan's scratch for `op` on `stream` (undefined if it needs none); a fresh buffer goes through purekv_workspace_init
 // once.  The caller holds the buffer until its launch is queued: while it is without the GIL, a call of another thread
 // that needs a larger one may replace it in the list.
 at::Tensor workspace(PlanObject* p, int op, hipStream_t stream, size_t nbytes, const at::Device& device, int32_t n_layers,
                      int32_t w, int32_t cap) {
   if (nbytes == 0) return {};
-  Workspace* slot = nullptr;
-  for (Workspace& x : *p->ws)
-    if (x.op == op && x.stream == stream) slot = &x;
-  if (slot != nullptr && (size_t)slot->t.numel() >= nbytes && slot->t.device() == device) return slot->t;
+  if (const Workspace* x = find_workspace(p, op, stream))
+    if ((size_t)x->t.numel() >= nbytes && x->t.device() == device) return x->t;
   at::Tensor t = at::empty({(int64_t)nbytes}, at::TensorOptions().dtype(at::kByte).device(device));
-  // (with the GIL: another thread must not change the list between the look-up and the entry)
   check(abi.workspace_init(p->plan, op, t.data_ptr(), nbytes, n_layers, w, cap, stream), "purekv_workspace_init");
-  if (slot == nullptr) p->ws->push_back({op, stream, t});
-  else slot->t = t;
+  // The allocation may have run Python code (a dispatch mode sees it), and with it other calls on this plan: the entry
+  // is looked up again, the list may have moved.
+  if (Workspace* x = find_workspace(p, op, stream)) x->t = t;
+  else p->ws->push_back({op, stream, t});
   return t;
 }
 

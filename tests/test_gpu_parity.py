@@ -843,6 +843,49 @@ def test_two_streams_share_one_plan():
             assert np.array_equal(bits_of(decs[i][rnd]), bits_of(decs[i][0]))
 
 
+def test_calls_from_inside_a_workspace_allocation():
+    """A dispatch mode sees the allocation of a workspace and calls the same plan on other streams meanwhile: their
+    buffers enter the plan's list while the outer call is about to replace its own, which was too small."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+    wl = SMALL["heads7_3f"]
+    plan, again = _plan(wl, 3), _plan(wl, 3)
+    hq, hkv, d = wl.n_q_heads, wl.n_kv_heads, wl.head_dim
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    q = torch.randn((hq, d), generator=gen, device="cuda").bfloat16()
+    short, long = (torch.randn((2, hkv, n, d), generator=gen, device="cuda").bfloat16() for n in (600, 5000))
+    out = torch.empty_like(q)
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    want_short, want_long = (pk.purekv_decode_attn(again, q, x[0], x[1], x.shape[2]) for x in (short, long))
+    pk.purekv_decode_attn(plan, q, short[0], short[1], 600, out=out)
+    torch.cuda.synchronize()
+    inner, empties = [], []
+
+    class Reenter(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            if func._schema.name.startswith("aten::empty"):
+                empties.append(tuple(args[0]))
+                if not inner:
+                    for s in streams:
+                        with torch.cuda.stream(s):
+                            inner.append(pk.purekv_decode_attn(plan, q, short[0], short[1], 600))
+            return func(*args, **(kwargs or {}))
+
+    with Reenter():
+        pk.purekv_decode_attn(plan, q, long[0], long[1], 5000, out=out)
+    torch.cuda.synchronize()
+    assert len(inner) == len(streams) and torch.equal(out, want_long)
+    assert all(torch.equal(x, want_short) for x in inner)
+    # every buffer is in the list: nothing is allocated again
+    n = len(empties)
+    with Reenter():
+        pk.purekv_decode_attn(plan, q, long[0], long[1], 5000, out=out)
+        for s, x in zip(streams, inner):
+            with torch.cuda.stream(s):
+                pk.purekv_decode_attn(plan, q, short[0], short[1], 600, out=x)
+    torch.cuda.synchronize()
+    assert len(empties) == n and torch.equal(out, want_long) and all(torch.equal(x, want_short) for x in inner)
+
+
 def test_an_output_that_does_not_fit_raises_out_of_memory():
     wl = SMALL["heads3_4f"]
     inp = generate(wl, seed=3)
