@@ -3,7 +3,7 @@
 // A workgroup owns 128 (or 192) non-recent keys of one KV head (32 per wavefront, held in registers as the
 // MFMA A operand for the whole kernel) and walks every window row of every query head of the group in
 // blocks of 32 rows.  The workgroup has two such sets of four (six) wavefronts: set 0 takes the even blocks, set 1 the
-// odd ones (two wavefronts per SIMD hide each other's LDS and MFMA latencies), and their sums are added at the
+// odd ones (the two or three wavefronts of a SIMD hide each other's LDS and MFMA latencies), and their sums are added at the
 // end in a fixed order.  The wavefronts of a set need the same query rows: a block of 32 rows (and its 32
 // log-sum-exp values) goes from global memory straight into a ring of six LDS slots per set
 // (global_load_lds: no staging registers), five blocks ahead of its use -- an iteration is a few hundred
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(128 * KW) void importance_kernel(const ImportanceAr
   // fragments were read from LDS during the previous stage, with, between them, the exponentials of block it - 1
   // (two scores per MFMA), the LDS reads of block it + 1's fragments and the start of the loads of block
   // it + NB - 1.  The matrix pipe, the vector ALU and LDS overlap although the one barrier per stage keeps all
-  // eight wavefronts in step.
+  // 2 KW wavefronts in step.
   struct Pending {   // what the exponentials of a block need besides its scores
     float neg_lse2;  // minus the log-sum-exp of the lane's row in log2 units; -inf when the row does not exist
     int rowc;        // the lane's row (clamped) and what the mask needs of it
@@ -290,11 +290,13 @@ int launch_importance(const purekv_plan& p, const void* q, const void* k, const 
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles(kw), (unsigned)p.g.Hkv), dim3(128u * kw), 0, st, a);
   };
   if (p.g.d == 128) {
-    // One workgroup per CU (LDS and registers): a launch of a few more than 256 takes two rounds.  Six wavefronts per set
-    // instead of four (three per SIMD instead of two) cost at most half as much again per round, so they are taken where the
-    // rounds saved make up for that: 4608 keys x 8 KV heads, 16 blocks of rows: 288 workgroups of four 21.2 us, 192 of six
-    // 15.3; 8192 keys x 4 KV heads are one full round of four (256 workgroups, 24 us).
-    auto cost = [&](int kw) { return (int64_t)kw * (((int64_t)tiles(kw) * p.g.Hkv + 255) / 256); };
+    // One workgroup per CU (LDS and registers): a launch of a few more than the chip has takes another round.  Six wavefronts
+    // per set instead of four (three per SIMD instead of two) take 1.2 to 1.3 times as long a round (at most 1.5 is
+    // assumed), so they are taken where the rounds saved make up for that.  256 CUs, both sides measured on 65 shapes of 8/8 to
+    // 28/4 heads: one round instead of two (264 to 384 workgroups of four) takes 0.64 to 0.73 of the time, three instead of five
+    // 0.81 to 0.85, five instead of eight 0.87 to 0.88 (8428 keys x 4 KV heads, 256 rows: 43.6 -> 28.0 us; 17516 x 8, 128
+    // rows: 48.7 -> 40.5); as many rounds as before take 1.20 to 1.29.
+    auto cost = [&](int kw) { return (int64_t)kw * (((int64_t)tiles(kw) * p.g.Hkv + p.n_cu - 1) / p.n_cu); };
     if (mask) launch(importance_kernel<128, true, 4>, 4);
     else if (cost(6) < cost(4)) launch(importance_kernel<128, false, 6>, 6);
     else launch(importance_kernel<128, false, 4>, 4);

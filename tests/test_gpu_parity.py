@@ -253,10 +253,10 @@ def test_importance_matches_oracle(name, pattern, w):
     assert np.all(got[ref == 0] == 0)
 
 
-@pytest.mark.parametrize("nv,w,hq,hkv", [(4100, 40, 8, 8), (2817, 31, 12, 12), (5569, 97, 12, 6)])
+@pytest.mark.parametrize("nv,w,hq,hkv", [(4100, 40, 8, 8), (2817, 31, 12, 12), (5569, 97, 12, 6), (3300, 40, 40, 40)])
 def test_importance_wide_workgroups(nv, w, hq, hkv):
     """Key counts whose 128-key tiles are a few more than the chip has compute units (264, 276, 264): 192 keys per workgroup
-    then, here with ragged last tiles and odd and even numbers of query blocks."""
+    then, here with ragged last tiles and odd and even numbers of query blocks; 1040 tiles: three rounds of 192 keys."""
     rng = np.random.default_rng(nv + w)
     n = nv + w
     from workloads import f32_to_bf16_bits

@@ -162,3 +162,20 @@ def test_token_major_layer_stack_equals_packed():
         assert np.array_equal(a[0][l], b[0][l])
     for x, y in zip(a[1:], b[1:]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("layout", [token_major, padded])
+def test_importance_wide_workgroups_strided(layout):
+    """The column sums' workgroups of 192 keys (264 tiles of 128 keys: a few more than the chip has compute units), on
+    strided Q and K."""
+    wl = small_variant("wide", n_frames=1, patch_h=4100, patch_w=1, n_text=40, n_q_heads=8, n_kv_heads=8, head_dim=128)
+    inp = generate(wl, seed=31)
+    q, k, v = to_dev(inp.q), to_dev(inp.k), to_dev(inp.v)
+    packed_plan = pk.Plan.for_workload(wl, 0)
+    _, lse = pk.purekv_st_spattn_prefill(packed_plan, q, k, v, want_lse=True)
+    c_p = pk.purekv_lowlayer_importance(packed_plan, q, k, lse, wl.window)
+    qv, kv, _, strides = layout(wl, q, k, v)
+    c_s = pk.purekv_lowlayer_importance(pk.Plan.for_workload(wl, 0, **strides), qv, kv, lse, wl.window)
+    assert torch.equal(c_s, c_p)
+    c_ref = orc.window_column_sums(F64(inp.q), F64(inp.k), 1, 4100, 40, 0, wl.window)
+    assert np.all(np.abs(f64_of(c_p) - c_ref) <= IMPORTANCE_REL * c_ref)
