@@ -305,7 +305,8 @@ def test_topk_row_lengths_across_kernel_variants(n_keys):
 @pytest.mark.parametrize("crowd", [1, 2, 31, 32, 33, 64])
 def test_topk_crowd_at_the_threshold(n_keys, crowd):
     """`crowd` keys that differ from each other in their last bits only (some of them equal), the h-th largest among them, in
-    rows that end inside a block of 1024: the radix passes end in a list of at most 32 candidates or in one pass more."""
+    rows that end inside a block of 1024: the radix passes end in a list of at most 32 candidates or in one pass more.
+    For each row, the h that ends just above its crowd, at the crowd's first, middle and last key, and just below."""
     if crowd > n_keys:
         pytest.skip("row shorter than the crowd")
     w = 8
@@ -319,12 +320,17 @@ def test_topk_crowd_at_the_threshold(n_keys, crowd):
     bits[0, at] = base + rng.integers(0, 256, crowd)     # distinct ones and ties
     bits[1, at] = base + np.arange(crowd)                # all distinct
     bits[2, at] = base + (np.arange(crowd) % 3 == 0)     # two values
-    first = int(min((s[k] > 0.7501).sum() for k in range(3)) - crowd)
-    for h in sorted({1, n_keys, max(1, first), first + 1 + crowd // 2, first + crowd}):
-        if 1 <= h <= n_keys:
+    for k in range(3):
+        above = int((s[k] > s[k, at].max()).sum())
+        in_crowd = {above + 1, above + (crowd + 1) // 2, above + crowd}
+        ranked = np.sort(s[k])[::-1]
+        for h in sorted({1, n_keys, above, above + crowd + 1} | in_crowd):
+            if not 1 <= h <= n_keys:
+                continue
+            assert h not in in_crowd or s[k, at].min() <= ranked[h - 1] <= s[k, at].max()
             idx = pk.purekv_topk_select(plan, torch.from_numpy(s).cuda(), None, w, h)
             ref = orc.topk_select(s.astype(np.float64), h, n_keys + w, w)
-            assert np.array_equal(idx.cpu().numpy(), ref), h
+            assert np.array_equal(idx.cpu().numpy(), ref), (k, h)
 
 
 def test_topk_negative_and_mixed_scores():
