@@ -173,9 +173,10 @@ __device__ __forceinline__ void block_scan2(uint32_t& a, uint32_t& b, uint32_t* 
 // A row is one workgroup's chain of barriers and LDS round trips; what counts is how many.  A pass has two (the histogram
 // has two buffers, the idle one is cleared behind the scan), the ranks of the kept keys one: ballots count the kept keys of
 // every 64 consecutive indices, and each wavefront scans the table of those counts by itself.
-// (A contiguous chunk of scores per thread staged through LDS, three barriers a pass and passes down to the last bit took 9.1
-// us for 8192 scores x 4 KV heads and 15 for 16384 x 4; this takes 7.6 and 11, of which the 16 wavefronts' vector
-// instructions on one CU are about half.)
+// (A contiguous chunk of scores per thread staged through LDS, three barriers a pass and passes down to the last bit took 9.0
+// us for 8192 log-normal scores x 4 KV heads and 14.7 for 16384 x 4, this 7.3 and 11.3: kernel trace, calls of this kernel
+// one after the other, median of 120.  Between the other kernels of a layer 8192 x 4 took 9.4 and take 8.9.  The 16
+// wavefronts' vector instructions on one CU are about half of it.)
 constexpr uint32_t SEL_LIST = 32;
 template <int EPT>
 __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __restrict__ s, int32_t* __restrict__ idx_out,
