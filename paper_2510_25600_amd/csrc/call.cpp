@@ -14,6 +14,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/device_lazy_init.h>
 
 #include <algorithm>
 #include <cstring>
@@ -71,7 +72,12 @@ struct PlanObject {
 
 PlanObject* as_plan(PyObject* o);
 
-hipStream_t current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+// torch's own initialisation comes first, as in torch.cuda.current_stream(): it refuses, with a RuntimeError, a process
+// without a GPU and one that was forked after its parent had initialised the GPU.
+hipStream_t current_stream() {
+  torch::utils::device_lazy_init(at::kCUDA);
+  return c10::hip::getCurrentHIPStream().stream();
+}
 
 bool is_none(PyObject* o) { return o == Py_None; }
 

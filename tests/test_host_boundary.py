@@ -461,6 +461,31 @@ def test_hot_calls_raise_the_types_of_torchs_exceptions():
     plan.close()
 
 
+@pytest.mark.skipif(torch.cuda.is_available(), reason="about a process whose GPU cannot be initialised")
+def test_calls_ask_torch_to_initialise_the_gpu(monkeypatch):
+    """Plan creation and the hot calls raise what torch.cuda.current_stream() raises: without a GPU, and in a process forked
+    after its parent had initialised the GPU."""
+    plan = pk.Plan(2, 4, 4, 8, 4, 2, 64, 3, host_only=True)
+    q, new, cache = _Refusing(4, 64), _Refusing(2, 64), _Refusing(2, 10, 64)
+    calls = [lambda: pk.Plan(2, 4, 4, 8, 4, 2, 64, 3), lambda: pk.purekv_decode_attn(plan, q, cache, cache, 10, out=q),
+             lambda: pk.purekv_decode_step(plan, q, new, new, cache, cache, 9, out=q)]
+
+    def raised(call):
+        with pytest.raises(RuntimeError) as e:
+            call()
+        return type(e.value), str(e.value)
+
+    want = raised(torch.cuda.current_stream)
+    assert all(raised(c) == want for c in calls)
+
+    def forked():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+    monkeypatch.setattr(torch.cuda, "_lazy_init", forked)
+    want = raised(torch.cuda.current_stream)
+    assert "forked" in want[1] and all(raised(c) == want for c in calls)
+    plan.close()
+
+
 @pytest.mark.parametrize("mask", [[0, 0, 0, 0, 1, 1, 1, 1], [1] * 8])
 def test_head_subset_of_whole_kv_groups_keeps_the_stacked_shape(mask):
     F, ph, pw, T, hq, hkv, d = 3, 6, 7, 300, 8, 2, 64
