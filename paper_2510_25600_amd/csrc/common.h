@@ -70,10 +70,13 @@ __device__ __forceinline__ void kunswz(int p, int& r, int& u) {
 // wave-uniform.  The LDS address travels in m0, which the statement overwrites (declared, so that the compiler
 // keeps nothing live in it across the load).
 typedef __attribute__((address_space(3))) void* LdsPtr;
-__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, const void* lds_ptr) {
-  const uint32_t lds_base = (uint32_t)(size_t)(LdsPtr)lds_ptr;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(off), "s"(base)
+__device__ __forceinline__ uint32_t lds_address(const void* lds_ptr) { return (uint32_t)(size_t)(LdsPtr)lds_ptr; }
+__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
                : "memory", "m0");
+}
+__device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, const void* lds_ptr) {
+  load_to_lds_16(base, off, lds_address(lds_ptr));
 }
 __device__ __forceinline__ void load_to_lds_4(const void* base, uint32_t off, const void* lds_ptr) {
   const uint32_t lds_base = (uint32_t)(size_t)(LdsPtr)lds_ptr;

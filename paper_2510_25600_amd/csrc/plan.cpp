@@ -138,7 +138,7 @@ void build_plan(purekv_plan& p, int n_cu) {
     const int32_t first_frame_tile = (g.P - 1) / BK;
     for (int32_t c = 0; c <= last_tile; ++c) {
       if (all_dense_rows && (c + 1) * BK - 1 <= r0) {
-        p.tiles.push_back({c, need_all, 0u});   // kind "full" is 0 in every field
+        p.tiles.push_back({c, need_all | kStepPlain, 0u});   // kind "full" is 0 in every field
         p.n_blocks += blocks_all;
         p.n_kind[kKindFull] += blocks_all;
         continue;
@@ -169,7 +169,7 @@ void build_plan(purekv_plan& p, int n_cu) {
           ++p.n_kind[kind];
         }
       }
-      if (need) p.tiles.push_back({c, need, kinds});
+      if (need) p.tiles.push_back({c, need | (need == need_all && kinds == 0u ? kStepPlain : 0u), kinds});
     }
     p.qtile_begin.push_back(static_cast<int32_t>(p.tiles.size()));
   }
@@ -435,13 +435,15 @@ void build_plan(purekv_plan& p, int n_cu) {
         e.kv_off = uint32_t((int64_t(kvh) * g.kv_sh + int64_t(r.tile) * BK * g.kv_st) * 2);
         const int32_t k0 = r.tile * BK, rows = std::min(BK, g.N - k0);
         uint8_t& own = owned[size_t(kvh) * size_t(n_ktiles) + size_t(r.tile)];
-        e.need = r.need | ((t == w.n_tiles - 1) ? (1u << 16) : 0u) | ((t == 0) ? (1u << 17) : 0u) |
-                 (uint32_t(rows - 1) << 18) | (own ? 0u : (1u << 24));
+        e.need = r.need | ((t == w.n_tiles - 1) ? kStepLast : 0u) | ((t == 0) ? kStepFirst : 0u) |
+                 (uint32_t(rows - 1) << 18) | (own ? 0u : kStepOwner);
         own = 1;
         e.kinds = r.kinds;
         e.k0 = k0;
         p.stream.push_back(e);
       }
+      if (u + 2 < queues[q].size())   // another unit follows
+        p.stream[p.stream.size() - (w.n_tiles >= 2 ? 2 : 1)].need |= kStepFetchQ;
     }
     p.queue_begin.push_back(static_cast<int32_t>(p.stream.size()));
     p.queue_units_begin.push_back(static_cast<int32_t>(p.queue_units.size() / 2));

@@ -40,7 +40,7 @@ struct MergeItem {
 };
 
 // One key tile of a query tile's list.  Bit 2*rb + kb of `need`: row block rb of the query tile has an allowed
-// pair among keys [tile*BK + 32*kb, +32).  Bits 4*rb + 2*kb, +1 of `kinds`: the BlockKind of that pair of blocks.
+// pair among keys [tile*BK + 32*kb, +32); bit 25 is kStepPlain.  Bits 4*rb + 2*kb, +1 of `kinds`: the BlockKind of that pair of blocks.
 struct TileRef {
   int32_t tile;
   uint32_t need;
@@ -53,10 +53,18 @@ struct StreamEntry {
   uint32_t need;       // TileRef::need | last << 16 | first << 17 | (rows - 1) << 18 | owner << 24: last / first step
                        // of its unit (units are numbered in stream order); rows = keys of the tile that exist
                        // (1..64); owner: this step is the one step of the launch that also emits the squared
-                       // norms of the tile's V rows (every (KV head, key tile) has exactly one owner step)
+                       // norms of the tile's V rows (every (KV head, key tile) has exactly one owner step);
+                       // | plain << 25 | fetch << 26 (kStepPlain, kStepFetchQ)
   uint32_t kinds;      // TileRef::kinds
   int32_t k0;          // first key of the tile
 };
+
+// Bits of StreamEntry::need that spare the kernel's loop its own tests (not part of the records that inspection calls return).
+constexpr uint32_t kStepLast = 1u << 16, kStepFirst = 1u << 17, kStepOwner = 1u << 24;
+constexpr uint32_t kStepPlain = 1u << 25;   // every row block that has rows needs both halves of the tile, without a mask
+constexpr uint32_t kStepFetchQ = 1u << 26;  // the query rows of the workgroup's next unit are requested during this step:
+                                            // the last but one of its unit (the only one of a unit of one step)
+constexpr uint32_t kStepPublic = kStepPlain - 1u;
 
 // A unit = work item x group of stacked query heads, run by one workgroup from its first to its last stream entry.
 struct Unit {

@@ -93,6 +93,26 @@ def test_prefill_matches_oracle(name, pattern):
         assert max(len(plan.queue(g)) for g in range(c["n_workgroups"])) >= 2  # some queue switches units
 
 
+@pytest.mark.parametrize("want_lse", [False, True])
+@pytest.mark.parametrize("dim", [64, 128])
+@pytest.mark.parametrize("frames,patch_h,patch_w,text", [(2, 5, 5, 0), (2, 7, 7, 2), (3, 7, 8, 12)])
+def test_prefill_units_of_one_to_three_steps(frames, patch_h, patch_w, text, dim, want_lse):
+    """Workgroups that run two or three units of one, two or three key tiles each: every step of such a queue begins or ends
+    a unit or requests the next one's query rows, and the pipeline never reaches its plain middle."""
+    wl = small_variant("short_units", n_frames=frames, patch_h=patch_h, patch_w=patch_w, n_text=text, n_q_heads=700,
+                       n_kv_heads=700, head_dim=dim)
+    inp = generate(wl, seed=5)
+    for pattern in (pk.PATTERN_DENSE, pk.PATTERN_ST):
+        plan = _plan(wl, pattern)
+        assert plan.counts()["n_workgroups"] < 700
+        got = pk.purekv_st_spattn_prefill(plan, to_dev(inp.q), to_dev(inp.k), to_dev(inp.v), want_lse=want_lse)
+        torch.cuda.synchronize()
+        ref, ref_lse = orc.masked_attention(F64(inp.q), F64(inp.k), F64(inp.v), wl.n_frames, wl.patches, wl.n_text, pattern)
+        check_attention(f64_of(got[0] if want_lse else got), ref, f"short units {wl.n_tokens}/d{dim}/p{pattern}")
+        if want_lse:
+            assert np.abs(f64_of(got[1]) - ref_lse).max() < 2e-3
+
+
 @pytest.mark.parametrize("pattern", [0, 3])
 @pytest.mark.parametrize("name,w", [("manyunits_g7", 190), ("manyunits_g7", 37), ("manyunits_g2", 120), ("manyunits_g2", 1),
                                     ("manyunits_g1", 100), ("manyunits_g1", 300), ("tiny_4f", 32), ("longtext_2f", 64)])
