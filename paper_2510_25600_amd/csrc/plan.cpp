@@ -7,8 +7,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstddef>
-#include <numeric>
+#include <functional>
+#include <queue>
 #include <utility>
+#include <vector>
 
 namespace purekv {
 
@@ -174,25 +176,22 @@ void build_plan(purekv_plan& p, int n_cu) {
     p.qtile_begin.push_back(static_cast<int32_t>(p.tiles.size()));
   }
 
-  // ---- cost model (in steps of one full tile) ----
-  // A tile of which every row block needs one 32-key half at most skips half of the score product; a unit
-  // switch (write the finished rows, reset the state, first tile without a second product to overlap) costs
-  // about one and a half steps.
-  // The slice that closes a split list (its workgroup runs it last, so it normally arrives last and combines the
-  // partial results of all slices) pays about two steps per slice for that (measured: a sweep of this constant on the 32-frame benchmark shape).
-  constexpr double kHalfTileCost = 0.85, kUnitCost = 1.5, kMergeCostPerSlice = 2.0;
-  std::vector<double> tile_cost(p.tiles.size());
+  // ---- cost model, in steps of one plain tile ----
+  // From the cycles of the workgroups of 22 shapes against what they ran: a half skipped saves MFMAs but no time, a step with
+  // the full predicate takes a tenth more; a unit (rows written, state reset, query rows fetched) as much as a step, 1.4
+  // with several heads of 128 stacked; a slice 1 more (fp32 rows through to memory, acknowledged) and, at the end of its
+  // queue, 1.5 for the look whether its list is complete; the workgroup that runs a list's closing slice, last in its queue,
+  // then combines it (2 us and 2 us a slice of 256 rows x 128: one CU reads them all).
+  constexpr double kGeneralCost = 1.1, kSliceCost = 2.5;
+  const double kUnitCost = g.Gs > 1 && g.d == 128 ? 1.4 : 1.0;
+  auto combine_cost = [&](int32_t n_slices) { return g.d == 128 ? 1.3 + 1.4 * n_slices : 1.0 + 0.7 * n_slices; };
+  std::vector<double> cost_before(p.tiles.size() + 1, 0.0);   // of the tiles before, in list order
   for (size_t i = 0; i < p.tiles.size(); ++i) {
-    bool both = false;
-    for (int32_t rb = 0; rb < g.R; ++rb) both |= ((p.tiles[i].need >> (2 * rb)) & 3u) == 3u;
-    tile_cost[i] = both ? 1.0 : kHalfTileCost;
+    const TileRef& t = p.tiles[i];
+    const bool general = (t.kinds & (t.kinds >> 1) & 0x55555555u) != 0u;
+    cost_before[i + 1] = cost_before[i] + (general ? kGeneralCost : 1.0);
   }
-
-  // ---- work items: cut lists that are long against the average load of one workgroup ----
   const double total_steps = double(p.tiles.size()) * n_groups_sel;
-  // Slice length: 0.8 of the average load of a workgroup (measured on the 32-frame benchmark shape: shorter
-  // slices balance no better after the refinement pass below and double the partial results to merge).
-  const int32_t chunk = std::max<int32_t>(8, static_cast<int32_t>(0.8 * total_steps / std::max(1, n_cu) + 0.5));
 
   // ---- window plans: the query tiles whose rows want the log-sum-exp get workgroups of their own ----
   // Only the last lse_rows rows are asked for their log-sum-exp (the recent window of Eq. 2).  Keeping the exact row
@@ -200,19 +199,19 @@ void build_plan(purekv_plan& p, int n_cu) {
   // hold such rows ("window tiles") are dealt to a set of workgroups of their own, sized by their share of the work,
   // and only those workgroups run the variant of the loop that keeps the sum.  A set of few workgroups needs units
   // small enough to be balanced over it: the window tiles' lists are cut into the number of slices that minimises an
-  // estimate of the set's longest queue (equal units dealt evenly, a unit switch per unit, the combination charged
-  // to the queue that closes a list), and the set is made large enough not to be the last to finish.
+  // estimate of the set's longest queue (equal units dealt evenly, the combination charged to the queue that closes a
+  // list), and the set is made large enough not to be the last to finish.
   // KV-head groups of the XCD affinity of the dealing below: workgroup q runs on XCD q % 8, and the units of a KV
   // head stay on the XCDs x with x % Hkv == kvh (Hkv < 8) or x == kvh % 8
   const int32_t affinity_groups = (p.head_sel.empty() && n_cu % 8 == 0 && (g.Hkv % 8 == 0 || 8 % g.Hkv == 0)) ? std::min(g.Hkv, 8) : 1;
   auto window_tile = [&](int32_t qt) {
     return p.lse_rows > 0 && int64_t(qt + 1) * rows_per_qtile > int64_t(g.N) - p.lse_rows;
   };
-  // measured on the 32-frame benchmark shape: a step that keeps the exact sum takes 1.10 of one that does not; a
-  // slice costs its workgroup about three steps more than a whole list does (partial result through to memory,
-  // arrival, the look at its list's counter at the end of the queue), on top of the combination itself
-  constexpr double kExactSumCost = 1.10, kSliceCost = 3.0;
-  int32_t n_window_queues = 0, window_slices = 1;
+  constexpr double kExactSumCost = 1.10;   // of a step that keeps the exact sum
+  struct WindowSet {
+    int32_t n_queues, slices;
+  };
+  std::vector<WindowSet> window_sets;   // candidates; {0, 1}: no workgroups of their own
   {
     double steps_w = 0;
     int64_t lists_w = 0;
@@ -237,7 +236,7 @@ void build_plan(purekv_plan& p, int n_cu) {
         for (int32_t ns = 1; ns <= std::min<int32_t>(kMaxSplits, std::max(1, shortest / 8)); ++ns) {
           const int64_t per_queue = (units_w * ns + nq - 1) / nq;
           const double longest = double(per_queue) * (len / ns + kUnitCost + (ns > 1 ? kSliceCost : 0.0)) +
-                                 (ns > 1 ? kMergeCostPerSlice * ns : 0.0);
+                                 (ns > 1 ? combine_cost(ns) : 0.0);
           if (ns == 1 || longest < best) best = longest, slices = ns;
         }
         return kExactSumCost * best;
@@ -248,100 +247,117 @@ void build_plan(purekv_plan& p, int n_cu) {
       // (a multiple of the number of KV-head groups of the XCD affinity below, so that every KV head keeps the same
       // number of workgroups in both sets)
       const int32_t nq0 = std::max<int32_t>(1, static_cast<int32_t>(cost_w / (cost_w + cost_rest) * n_cu));
+      const int32_t nq_first = (nq0 + affinity_groups - 1) / affinity_groups * affinity_groups;
+      const int32_t nq_last = std::min<int32_t>(n_cu - 1, 2 * nq0 + 8 + affinity_groups);
+      WindowSet best{0, 1};
       double best_end = 0;
-      for (int32_t nq = (nq0 + affinity_groups - 1) / affinity_groups * affinity_groups;
-           nq <= std::min<int32_t>(n_cu - 1, 2 * nq0 + 8 + affinity_groups); nq += affinity_groups) {
+      for (int32_t nq = nq_first; nq <= nq_last; nq += affinity_groups) {
         int32_t slices = 1;
         const double end_w = window_set(nq, slices), end_r = rest_set(nq), end = std::max(end_w, end_r);
-        if (n_window_queues == 0 || end < best_end) best_end = end, n_window_queues = nq, window_slices = slices;
+        if (best.n_queues == 0 || end < best_end) best_end = end, best = {nq, slices};
         if (end_w <= end_r) break;
       }
-    }
-  }
-  p.items.clear();
-  p.merges.clear();
-  p.n_slots = 0;
-  for (int32_t qt = 0; qt < p.n_qtiles; ++qt) {
-    const int32_t b = p.qtile_begin[qt], len = p.qtile_begin[qt + 1] - b;
-    int32_t ns = 1;
-    if (2 * len > 3 * chunk) ns = std::min<int32_t>((len + chunk - 1) / chunk, kMaxSplits);
-    if (n_window_queues > 0 && window_tile(qt)) ns = std::min(window_slices, std::max(1, len / 8));
-    if (ns == 1) {
-      p.items.push_back({qt, b, len, 0, 1, -1});
-      continue;
-    }
-    p.merges.push_back({qt, p.n_slots, ns, 0});
-    int32_t pos = b;
-    for (int32_t s = 0; s < ns; ++s) {
-      const int32_t cnt = len / ns + (s < len % ns ? 1 : 0);
-      p.items.push_back({qt, pos, cnt, s, ns, p.n_slots + s});
-      pos += cnt;
-    }
-    p.n_slots += ns;
-  }
-  std::stable_sort(p.items.begin(), p.items.end(),
-                   [](const WorkItem& x, const WorkItem& y) { return x.n_tiles > y.n_tiles; });
-  std::vector<double> item_cost(p.items.size());
-  for (size_t it = 0; it < p.items.size(); ++it) {
-    double c = kUnitCost;
-    for (int32_t t = 0; t < p.items[it].n_tiles; ++t) c += tile_cost[p.items[it].list_begin + t];
-    if (p.items[it].n_splits > 1 && p.items[it].split == p.items[it].n_splits - 1)
-      c += kMergeCostPerSlice * p.items[it].n_splits;
-    item_cost[it] = c;
-  }
-
-  // ---- deal (item, head group) units onto persistent workgroups: longest first, least-loaded queue ----
-  // Workgroup q runs on XCD q % 8 (round-robin dispatch); when the head counts allow it, the units of one
-  // KV head stay on a fixed set of XCDs so that each L2 holds the K/V of few KV heads.
-  const int64_t n_units = int64_t(p.items.size()) * n_groups_sel;
-  p.n_queues = static_cast<int32_t>(std::min<int64_t>(std::max(1, n_cu), std::max<int64_t>(1, n_units)));
-  auto item_class = [&](int32_t it) { return (n_window_queues > 0 && window_tile(p.items[it].qtile)) ? 1 : 0; };
-  if (n_window_queues > 0) {
-    int64_t units_w = 0;
-    for (size_t it = 0; it < p.items.size(); ++it) units_w += item_class(static_cast<int32_t>(it)) * n_groups_sel;
-    n_window_queues = static_cast<int32_t>(std::min<int64_t>(n_window_queues, units_w));
-  }
-  // queues [0, lse_queue0): units of the other tiles; [lse_queue0, n_queues): units of the window tiles.  A plan
-  // without a window keeps one class: every workgroup keeps the exact sum when the log-sum-exp is asked for.
-  p.lse_queue0 = n_window_queues > 0 ? p.n_queues - n_window_queues : 0;
-  // (not for a head subset: its KV heads may be few, and every queue has to receive a unit)
-  const bool affinity = p.head_sel.empty() && (p.n_queues % 8 == 0) && (g.Hkv % 8 == 0 || 8 % g.Hkv == 0);
-  std::vector<std::vector<int32_t>> queues(p.n_queues);  // flat (item, group) pairs
-  std::vector<double> load(p.n_queues, 0.0);
-  auto deal_class = [&](int cls, int32_t q_lo, int32_t q_hi) {
-    // the affinity needs the same number of queues for every KV head inside the range (the sets of a divided plan
-    // are sized for that)
-    const bool aff = affinity && (q_hi - q_lo) % affinity_groups == 0;
-    auto allowed = [&](int32_t q, int32_t kvh) {
-      if (!aff) return true;
-      const int32_t x = q % 8;
-      return (g.Hkv >= 8) ? (x == kvh % 8) : (x % g.Hkv == kvh);
-    };
-    for (size_t it = 0; it < p.items.size(); ++it) {
-      if (item_class(static_cast<int32_t>(it)) != cls) continue;
-      for (int32_t grp = 0; grp < g.n_groups; ++grp) {
-        if (!group_selected(grp)) continue;
-        const int32_t kvh = grp * g.Gs / g.G;
-        int32_t best = -1;
-        for (int32_t q = q_lo; q < q_hi; ++q)
-          if (allowed(q, kvh) && (best < 0 || load[q] < load[best])) best = q;
-        queues[best].push_back(static_cast<int32_t>(it));
-        queues[best].push_back(grp);
-        load[best] += item_cost[it];
+      // a neighbouring size may suit the other set's units better: the dealing below decides
+      for (int32_t nq : {best.n_queues, best.n_queues - affinity_groups, best.n_queues + affinity_groups}) {
+        if (nq < nq_first || nq > nq_last) continue;
+        int32_t slices = 1;
+        (void)window_set(nq, slices);
+        window_sets.push_back({nq, slices});
       }
     }
-    // Refinement: while it lowers the larger of the two loads, move a unit from the fullest queue to the emptiest
-    // queue that may run it, or exchange a unit of each.
+  }
+  if (window_sets.empty()) window_sets.push_back({0, 1});
+
+  // ---- schedules: cut lists that are long against the average load, deal the units, keep the schedule that ends first ----
+  struct Schedule {
+    std::vector<WorkItem> items;
+    std::vector<MergeItem> merges;
+    std::vector<double> item_cost;
+    std::vector<std::vector<int32_t>> queues;   // flat (item, group) pairs
+    std::vector<double> load;
+    std::vector<int32_t> slices;                // per query tile
+    int32_t n_slots = 0, n_queues = 0, lse_queue0 = 0;
+    double end = 0;                             // predicted, of the last queue
+  };
+  auto cut = [&](Schedule& s, double factor, const WindowSet& ws) {
+    const int32_t chunk = std::max<int32_t>(8, static_cast<int32_t>(std::min(factor * total_steps / std::max(1, n_cu) + 0.5, 1e9)));
+    for (int32_t qt = 0; qt < p.n_qtiles; ++qt) {
+      const int32_t b = p.qtile_begin[qt], len = p.qtile_begin[qt + 1] - b;
+      int32_t ns = 1;
+      if (2 * int64_t(len) > 3 * int64_t(chunk)) ns = std::min<int32_t>((len + chunk - 1) / chunk, kMaxSplits);
+      if (ws.n_queues > 0 && window_tile(qt)) ns = std::min(ws.slices, std::max(1, len / 8));
+      s.slices.push_back(ns);
+      if (ns == 1) {
+        s.items.push_back({qt, b, len, 0, 1, -1});
+        continue;
+      }
+      s.merges.push_back({qt, s.n_slots, ns, 0});
+      int32_t pos = b;
+      for (int32_t i = 0; i < ns; ++i) {
+        const int32_t cnt = len / ns + (i < len % ns ? 1 : 0);
+        s.items.push_back({qt, pos, cnt, i, ns, s.n_slots + i});
+        pos += cnt;
+      }
+      s.n_slots += ns;
+    }
+    std::stable_sort(s.items.begin(), s.items.end(),
+                     [](const WorkItem& x, const WorkItem& y) { return x.n_tiles > y.n_tiles; });
+    for (const WorkItem& w : s.items) {
+      double c = kUnitCost + cost_before[w.list_begin + w.n_tiles] - cost_before[w.list_begin];
+      if (w.n_splits > 1) c += kSliceCost + (w.split == w.n_splits - 1 ? combine_cost(w.n_splits) : 0.0);
+      s.item_cost.push_back(c);
+    }
+  };
+  // Units are dealt longest first, each to the least-loaded queue that may run it.  Workgroup q runs on XCD q % 8
+  // (round-robin dispatch); when the head counts allow it, the units of one KV head stay on a fixed set of XCDs so
+  // that each L2 holds the K/V of few KV heads.  Queues [0, lse_queue0) hold the units of the other tiles, [lse_queue0,
+  // n_queues) those of the window tiles; a plan without a window keeps one class: every workgroup keeps the exact sum when
+  // the log-sum-exp is asked for.
+  auto item_class = [&](const Schedule& s, size_t it) { return s.lse_queue0 > 0 && window_tile(s.items[it].qtile) ? 1 : 0; };
+  auto affine = [&](const Schedule& s, int32_t q_lo, int32_t q_hi) {
+    // (not for a head subset: its KV heads may be few, and every queue has to receive a unit; and only with the same number
+    // of queues for every KV head inside the range: the sets of a divided plan are sized for that)
+    return p.head_sel.empty() && s.n_queues % 8 == 0 && (g.Hkv % 8 == 0 || 8 % g.Hkv == 0) && (q_hi - q_lo) % affinity_groups == 0;
+  };
+  auto home_of_queue = [&](int32_t q) { return g.Hkv >= 8 ? q % 8 : q % 8 % g.Hkv; };
+  auto home_of_group = [&](int32_t grp) { return g.Hkv >= 8 ? grp * g.Gs / g.G % 8 : grp * g.Gs / g.G; };
+  auto deal_class = [&](Schedule& s, int cls, int32_t q_lo, int32_t q_hi, bool loads_only) {
+    const bool aff = affine(s, q_lo, q_hi);
+    typedef std::pair<double, int32_t> LoadQueue;   // least loaded first, then lowest index
+    std::vector<std::priority_queue<LoadQueue, std::vector<LoadQueue>, std::greater<LoadQueue>>> by_home(aff ? 8 : 1);
+    for (int32_t q = q_lo; q < q_hi; ++q) by_home[aff ? home_of_queue(q) : 0].push({0.0, q});
+    for (size_t it = 0; it < s.items.size(); ++it) {
+      if (item_class(s, it) != cls) continue;
+      for (int32_t grp = 0; grp < g.n_groups; ++grp) {
+        if (!group_selected(grp)) continue;
+        auto& heap = by_home[aff ? home_of_group(grp) : 0];
+        LoadQueue lq = heap.top();
+        heap.pop();
+        if (!loads_only) {
+          s.queues[lq.second].push_back(static_cast<int32_t>(it));
+          s.queues[lq.second].push_back(grp);
+        }
+        lq.first = s.load[lq.second] += s.item_cost[it];
+        heap.push(lq);
+      }
+    }
+  };
+  // Refinement: while it lowers the larger of the two loads, move a unit from the fullest queue to another queue that may
+  // run it, or exchange a unit of each.
+  auto refine_class = [&](Schedule& s, int32_t q_lo, int32_t q_hi) {
+    const bool aff = affine(s, q_lo, q_hi);
+    auto& queues = s.queues;
+    auto& load = s.load;
+    auto allowed = [&](int32_t q, int32_t grp) { return !aff || home_of_queue(q) == home_of_group(grp); };
     for (int32_t round = 0; round < 8 * (q_hi - q_lo); ++round) {
       const int32_t qa = static_cast<int32_t>(std::max_element(load.begin() + q_lo, load.begin() + q_hi) - load.begin());
       double best_gain = 1e-9;
       int32_t best_q = -1;
       size_t best_u = 0, best_v = SIZE_MAX;
       for (size_t u = 0; u + 1 < queues[qa].size(); u += 2) {
-        const double cu = item_cost[queues[qa][u]];
-        const int32_t kvh = queues[qa][u + 1] * g.Gs / g.G;
+        const double cu = s.item_cost[queues[qa][u]];
         for (int32_t qb = q_lo; qb < q_hi; ++qb) {
-          if (qb == qa || !allowed(qb, kvh)) continue;
+          if (0.5 * (load[qa] - load[qb]) <= best_gain || !allowed(qb, queues[qa][u + 1])) continue;   // (no larger gain there)
           // move u: new pair maximum = max(load[qa] - cu, load[qb] + cu)
           double gain = load[qa] - std::max(load[qa] - cu, load[qb] + cu);
           if (gain > best_gain) {
@@ -351,8 +367,8 @@ void build_plan(purekv_plan& p, int n_cu) {
             best_v = SIZE_MAX;
           }
           for (size_t v = 0; v + 1 < queues[qb].size(); v += 2) {
-            const double cv = item_cost[queues[qb][v]];
-            if (cv >= cu || !allowed(qa, queues[qb][v + 1] * g.Gs / g.G)) continue;
+            const double cv = s.item_cost[queues[qb][v]];
+            if (cv >= cu || !allowed(qa, queues[qb][v + 1])) continue;
             gain = load[qa] - std::max(load[qa] - cu + cv, load[qb] + cu - cv);
             if (gain > best_gain) {
               best_gain = gain;
@@ -369,25 +385,72 @@ void build_plan(purekv_plan& p, int n_cu) {
         queues[qa].erase(queues[qa].begin() + best_u, queues[qa].begin() + best_u + 2);
         queues[best_q].push_back(ui);
         queues[best_q].push_back(ug);
-        load[qa] -= item_cost[ui];
-        load[best_q] += item_cost[ui];
+        load[qa] -= s.item_cost[ui];
+        load[best_q] += s.item_cost[ui];
       } else {
         const int32_t vi = queues[best_q][best_v], vg = queues[best_q][best_v + 1];
         queues[qa][best_u] = vi;
         queues[qa][best_u + 1] = vg;
         queues[best_q][best_v] = ui;
         queues[best_q][best_v + 1] = ug;
-        load[qa] += item_cost[vi] - item_cost[ui];
-        load[best_q] += item_cost[ui] - item_cost[vi];
+        load[qa] += s.item_cost[vi] - s.item_cost[ui];
+        load[best_q] += s.item_cost[ui] - s.item_cost[vi];
       }
     }
   };
-  if (n_window_queues > 0) {
-    deal_class(0, 0, p.lse_queue0);
-    deal_class(1, p.lse_queue0, p.n_queues);
-  } else {
-    deal_class(0, 0, p.n_queues);
+  auto make = [&](double factor, const WindowSet& ws, bool loads_only) {
+    Schedule s;
+    cut(s, factor, ws);
+    const int64_t n_units = int64_t(s.items.size()) * n_groups_sel;
+    s.n_queues = static_cast<int32_t>(std::min<int64_t>(std::max(1, n_cu), std::max<int64_t>(1, n_units)));
+    int64_t units_w = 0;
+    if (ws.n_queues > 0)
+      for (const WorkItem& w : s.items) units_w += window_tile(w.qtile) ? n_groups_sel : 0;
+    s.lse_queue0 = ws.n_queues > 0 ? s.n_queues - static_cast<int32_t>(std::min<int64_t>(ws.n_queues, units_w)) : 0;
+    if (!loads_only) s.queues.resize(s.n_queues);
+    s.load.assign(s.n_queues, 0.0);
+    const int32_t q_split = s.lse_queue0 > 0 ? s.lse_queue0 : s.n_queues;
+    if (q_split < s.n_queues) deal_class(s, 1, q_split, s.n_queues, loads_only);
+    deal_class(s, 0, 0, q_split, loads_only);
+    if (!loads_only) {
+      if (q_split < s.n_queues) refine_class(s, q_split, s.n_queues);
+      refine_class(s, 0, q_split);
+    }
+    s.end = 0;
+    for (int32_t q = 0; q < s.n_queues; ++q) s.end = std::max(s.end, s.load[q] * (q >= q_split ? kExactSumCost : 1.0));
+    return s;
+  };
+  // Slice lengths, as factors of the average load of a workgroup.  None suits all: whole lists leave a shape with few units
+  // per workgroup with a long tail, short slices cost unit switches and combinations.  0.8 unless another one ends 3 %
+  // sooner by the model, whose workgroups' ends scatter by as much.  Prefill alone, always 0.8 and the model before it -> this:
+  // dense, 14 frames of 19 x 8 patches + 51 tokens, 28/4 heads of 128: 65.2 -> 53.7 us; 11 of 22 x 11 + 10, 8/8 of 64: 33.7 ->
+  // 25.0; sparse, 55 of 24 x 8 + 264, 8/8 of 128: 75.3 -> 61.1; 6 of 22 x 19 + 22, 28/4 of 64: 32.5 -> 26.5; 66 drawn shapes 0.97
+  // in the mean, at most 1.04.
+  // Plans with three and more units per workgroup balance with any of them and take 0.8 without a search.  The search deals
+  // loads only, 0.05 ms a factor; the schedule it finds is dealt in full and refined like the first.
+  constexpr double kSliceFactor = 0.8, kOtherFactors[] = {0.4, 0.55, 0.65, 1.0, 1.25, 1.6, 1e9}, kSooner = 1.03;
+  Schedule chosen = make(kSliceFactor, window_sets[0], false);
+  if (int64_t(p.n_qtiles) * n_groups_sel <= 3 * int64_t(n_cu)) {
+    double other_end = make(kSliceFactor, window_sets[0], true).end / kSooner, other_factor = 0;
+    WindowSet other_set = window_sets[0];
+    auto consider = [&](double factor, const WindowSet& ws) {
+      const double end = make(factor, ws, true).end;
+      if (end < other_end) other_end = end, other_factor = factor, other_set = ws;
+    };
+    for (size_t i = 1; i < window_sets.size(); ++i) consider(kSliceFactor, window_sets[i]);
+    const WindowSet ws = other_set;
+    for (double factor : kOtherFactors) consider(factor, ws);
+    if (other_factor > 0) {
+      Schedule other = make(other_factor, other_set, false);
+      if (other.end * kSooner < chosen.end) chosen = std::move(other);
+    }
   }
+  p.items = std::move(chosen.items);
+  p.merges = std::move(chosen.merges);
+  p.n_slots = chosen.n_slots;
+  p.n_queues = chosen.n_queues;
+  p.lse_queue0 = chosen.lse_queue0;
+  std::vector<std::vector<int32_t>>& queues = chosen.queues;
   // Order within a queue: slices of split lists first, except the closing slice of a list, which goes last (when it
   // ends, the other slices of its list, run first elsewhere, have normally long arrived: the workgroup that the
   // cost model charged for combining them is then the one that does); whole lists in between, longest first (item
