@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstddef>
 #include <functional>
+#include <limits>
 #include <queue>
 #include <utility>
 #include <vector>
@@ -275,9 +276,8 @@ void build_plan(purekv_plan& p, int n_cu) {
     std::vector<double> item_cost;
     std::vector<std::vector<int32_t>> queues;   // flat (item, group) pairs
     std::vector<double> load;
-    std::vector<int32_t> slices;                // per query tile
     int32_t n_slots = 0, n_queues = 0, lse_queue0 = 0;
-    double end = 0;                             // predicted, of the last queue
+    double dealt_end = 0, end = 0;              // predicted, of the last queue, before and after the refinement
   };
   auto cut = [&](Schedule& s, double factor, const WindowSet& ws) {
     const int32_t chunk = std::max<int32_t>(8, static_cast<int32_t>(std::min(factor * total_steps / std::max(1, n_cu) + 0.5, 1e9)));
@@ -286,7 +286,6 @@ void build_plan(purekv_plan& p, int n_cu) {
       int32_t ns = 1;
       if (2 * int64_t(len) > 3 * int64_t(chunk)) ns = std::min<int32_t>((len + chunk - 1) / chunk, kMaxSplits);
       if (ws.n_queues > 0 && window_tile(qt)) ns = std::min(ws.slices, std::max(1, len / 8));
-      s.slices.push_back(ns);
       if (ns == 1) {
         s.items.push_back({qt, b, len, 0, 1, -1});
         continue;
@@ -356,6 +355,10 @@ void build_plan(purekv_plan& p, int n_cu) {
       size_t best_u = 0, best_v = SIZE_MAX;
       for (size_t u = 0; u + 1 < queues[qa].size(); u += 2) {
         const double cu = s.item_cost[queues[qa][u]];
+        bool seen = false;   // a unit of the same cost that may go to the same queues
+        for (size_t x = 0; x < u && !seen; x += 2)
+          seen = s.item_cost[queues[qa][x]] == cu && (!aff || home_of_group(queues[qa][x + 1]) == home_of_group(queues[qa][u + 1]));
+        if (seen) continue;
         for (int32_t qb = q_lo; qb < q_hi; ++qb) {
           if (0.5 * (load[qa] - load[qb]) <= best_gain || !allowed(qb, queues[qa][u + 1])) continue;   // (no larger gain there)
           // move u: new pair maximum = max(load[qa] - cu, load[qb] + cu)
@@ -398,7 +401,8 @@ void build_plan(purekv_plan& p, int n_cu) {
       }
     }
   };
-  auto make = [&](double factor, const WindowSet& ws, bool loads_only) {
+  // `limit`: a schedule whose queues end no sooner on average, or whose longest unit does not, is given up undealt.
+  auto make = [&](double factor, const WindowSet& ws, bool loads_only, double limit) {
     Schedule s;
     cut(s, factor, ws);
     const int64_t n_units = int64_t(s.items.size()) * n_groups_sel;
@@ -407,17 +411,30 @@ void build_plan(purekv_plan& p, int n_cu) {
     if (ws.n_queues > 0)
       for (const WorkItem& w : s.items) units_w += window_tile(w.qtile) ? n_groups_sel : 0;
     s.lse_queue0 = ws.n_queues > 0 ? s.n_queues - static_cast<int32_t>(std::min<int64_t>(ws.n_queues, units_w)) : 0;
+    const int32_t q_split = s.lse_queue0 > 0 ? s.lse_queue0 : s.n_queues;
+    double sum[2] = {0, 0}, longest[2] = {0, 0};   // per class
+    for (size_t it = 0; it < s.items.size(); ++it) {
+      const int cls = item_class(s, it);
+      sum[cls] += s.item_cost[it] * n_groups_sel;
+      longest[cls] = std::max(longest[cls], s.item_cost[it]);
+    }
+    s.end = std::max(sum[0] / q_split, longest[0]);
+    if (q_split < s.n_queues) s.end = std::max(s.end, kExactSumCost * std::max(sum[1] / (s.n_queues - q_split), longest[1]));
+    if (s.end >= limit) return s;
     if (!loads_only) s.queues.resize(s.n_queues);
     s.load.assign(s.n_queues, 0.0);
-    const int32_t q_split = s.lse_queue0 > 0 ? s.lse_queue0 : s.n_queues;
+    auto last_end = [&]() {
+      double end = 0;
+      for (int32_t q = 0; q < s.n_queues; ++q) end = std::max(end, s.load[q] * (q >= q_split ? kExactSumCost : 1.0));
+      return end;
+    };
     if (q_split < s.n_queues) deal_class(s, 1, q_split, s.n_queues, loads_only);
     deal_class(s, 0, 0, q_split, loads_only);
-    if (!loads_only) {
-      if (q_split < s.n_queues) refine_class(s, q_split, s.n_queues);
-      refine_class(s, 0, q_split);
-    }
-    s.end = 0;
-    for (int32_t q = 0; q < s.n_queues; ++q) s.end = std::max(s.end, s.load[q] * (q >= q_split ? kExactSumCost : 1.0));
+    s.dealt_end = s.end = last_end();
+    if (loads_only) return s;
+    if (q_split < s.n_queues) refine_class(s, q_split, s.n_queues);
+    refine_class(s, 0, q_split);
+    s.end = last_end();
     return s;
   };
   // Slice lengths, as factors of the average load of a workgroup.  None suits all: whole lists leave a shape with few units
@@ -426,22 +443,27 @@ void build_plan(purekv_plan& p, int n_cu) {
   // dense, 14 frames of 19 x 8 patches + 51 tokens, 28/4 heads of 128: 65.2 -> 53.7 us; 11 of 22 x 11 + 10, 8/8 of 64: 33.7 ->
   // 25.0; sparse, 55 of 24 x 8 + 264, 8/8 of 128: 75.3 -> 61.1; 6 of 22 x 19 + 22, 28/4 of 64: 32.5 -> 26.5; 66 drawn shapes 0.97
   // in the mean, at most 1.04.
-  // Plans with three and more units per workgroup balance with any of them and take 0.8 without a search.  The search deals
-  // loads only, 0.05 ms a factor; the schedule it finds is dealt in full and refined like the first.
+  // Plans with more than three units per workgroup balance with any of them and take 0.8 without a search, as do those whose
+  // first schedule ends within 3 % of the average load of uncut lists.  The search deals loads only, 0.05 ms a factor, and
+  // no schedule that the one in hand beats on the average already; the one it finds is dealt in full and refined like the
+  // first.  Planning 32 shapes, one length always -> with the search: 23.4 -> 19.3 ms in all (heaps pay for it); sparse, 64
+  // frames of 16 x 16, 5.7 -> 2.1; dense window plan, 8 frames of 24 x 24 + 128, 32/8 heads, 0.39 -> 0.72.
   constexpr double kSliceFactor = 0.8, kOtherFactors[] = {0.4, 0.55, 0.65, 1.0, 1.25, 1.6, 1e9}, kSooner = 1.03;
-  Schedule chosen = make(kSliceFactor, window_sets[0], false);
-  if (int64_t(p.n_qtiles) * n_groups_sel <= 3 * int64_t(n_cu)) {
-    double other_end = make(kSliceFactor, window_sets[0], true).end / kSooner, other_factor = 0;
+  const double kNoLimit = std::numeric_limits<double>::infinity();
+  Schedule chosen = make(kSliceFactor, window_sets[0], false, kNoLimit);
+  const double no_sooner = (cost_before.back() + kUnitCost * p.n_qtiles) * n_groups_sel / std::max(1, n_cu);
+  if (int64_t(p.n_qtiles) * n_groups_sel <= 3 * int64_t(n_cu) && chosen.end > kSooner * no_sooner) {
+    double other_end = chosen.dealt_end / kSooner, other_factor = 0;
     WindowSet other_set = window_sets[0];
     auto consider = [&](double factor, const WindowSet& ws) {
-      const double end = make(factor, ws, true).end;
+      const double end = make(factor, ws, true, other_end).end;
       if (end < other_end) other_end = end, other_factor = factor, other_set = ws;
     };
     for (size_t i = 1; i < window_sets.size(); ++i) consider(kSliceFactor, window_sets[i]);
     const WindowSet ws = other_set;
     for (double factor : kOtherFactors) consider(factor, ws);
     if (other_factor > 0) {
-      Schedule other = make(other_factor, other_set, false);
+      Schedule other = make(other_factor, other_set, false, kNoLimit);
       if (other.end * kSooner < chosen.end) chosen = std::move(other);
     }
   }

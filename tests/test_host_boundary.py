@@ -347,6 +347,18 @@ def test_window_plans_small(shape, pattern, window):
     _check_plan_against_oracle(F, ph, pw, T, 4, 2, 64, pattern, n_wg=16, window=window)
 
 
+@pytest.mark.parametrize("n_wg", [250, 256])
+@pytest.mark.parametrize("window", [0, 20])
+@pytest.mark.parametrize("pattern", [0, 3])
+@pytest.mark.parametrize("shape,heads,dim", [((9, 15, 21, 93), (24, 8), 64), ((11, 11, 11, 40), (8, 8), 64),
+                                             ((6, 22, 19, 40), (28, 4), 64), ((5, 8, 8, 40), (24, 8), 128)])
+def test_plans_of_searched_slice_lengths(shape, heads, dim, pattern, window, n_wg):
+    """At most three units per workgroup: the planner tries other slice lengths and sizes of the window set, also where the
+    workgroups (250) do not divide among the XCDs."""
+    F, ph, pw, T = shape
+    _check_plan_against_oracle(F, ph, pw, T, heads[0], heads[1], dim, pattern, n_wg=n_wg, window=window)
+
+
 def test_window_plan_argument_errors():
     lib = pk.raw()
     shape = pk.Shape(4, 8, 8, 32, 4, 2, 64, 3, 0.0, 0, 0, 0, 0, 0, 0)
