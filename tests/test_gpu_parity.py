@@ -237,6 +237,38 @@ def test_prefill_reference_is_raised(pattern, d, step):
     assert (np.abs(f64_of(lse) - ref_lse) <= 2e-3 + 2.0 ** -21 * np.abs(ref_lse)).all()
 
 
+@pytest.mark.parametrize("pattern", [0, 3])
+@pytest.mark.parametrize("frames,patch_h,patch_w,text,dim", [(3, 9, 11, 700, 128), (2, 16, 16, 600, 64)])
+def test_prefill_rows_whose_scores_are_all_minus_infinity(frames, patch_h, patch_w, text, dim, pattern):
+    """A row none of whose scores is finite has no weights: its output is 0 and its log-sum-exp -inf, whether its key list
+    is run whole or in slices; and a slice without a finite score adds nothing to the others."""
+    from workloads import f32_to_bf16_bits
+    wl = small_variant("minus_inf", n_frames=frames, patch_h=patch_h, patch_w=patch_w, n_text=text, n_q_heads=4, n_kv_heads=2,
+                       head_dim=dim)
+    n, half = wl.n_tokens, wl.n_tokens // 2
+    rng = np.random.default_rng(dim)
+    q, k, v = (rng.standard_normal((h, n, dim)).astype(np.float32) for h in (4, 2, 2))
+    q[:, :, 0] = 1.0
+    k[:, :, 0] = 0.0
+    k[0, :, 0], k[1, :half, 0] = -np.inf, -np.inf     # no key of KV head 0 has a finite score, no key before `half` of 1
+    qb, kb, vb = (f32_to_bf16_bits(x) for x in (q, k, v))
+    plan = _plan(wl, pattern)
+    assert plan.counts()["n_split_qtiles"] > 0 and any(plan.item(i)[4] == 1 for i in range(plan.counts()["n_items"]))
+    out, lse = pk.purekv_st_spattn_prefill(plan, to_dev(qb), to_dev(kb), to_dev(vb), want_lse=True)
+    torch.cuda.synchronize()
+    out, lse = f64_of(out), f64_of(lse)
+    mask = orc.st_mask(frames, patch_h * patch_w, text, pattern)
+    dead = ~mask[:, half:].any(axis=1)                # rows of the second KV head's query heads without a finite score
+    assert dead.any() and not dead.all()
+    assert not out[:2].any() and np.isneginf(lse[:2]).all()
+    assert not out[2:, dead].any() and np.isneginf(lse[2:, dead]).all()
+    kf = F64(kb)
+    kf[:, :, 0] = np.where(np.isneginf(kf[:, :, 0]), -1e9, 0.0)
+    ref, ref_lse = orc.masked_attention(F64(qb), kf, F64(vb), frames, patch_h * patch_w, text, pattern)
+    check_attention(out[2:, ~dead], ref[2:, ~dead], f"-inf scores d={dim} p={pattern}")
+    assert np.abs(lse[2:, ~dead] - ref_lse[2:, ~dead]).max() < 2e-3
+
+
 def test_prefill_custom_scale():
     wl = SMALL["ragged_3f"]
     inp = generate(wl, seed=5)
