@@ -270,12 +270,19 @@ void build_plan(purekv_plan& p, int n_cu) {
   if (window_sets.empty()) window_sets.push_back({0, 1});
 
   // ---- schedules: cut lists that are long against the average load, deal the units, keep the schedule that ends first ----
+  // Workgroup q runs on XCD q % 8 (round-robin dispatch); when the head counts allow it, the units of one KV head stay on a
+  // fixed set of XCDs, a home, so that each L2 holds the K/V of few KV heads.  Homes have equally many queues and the same
+  // units, one for each of their head groups: one home is dealt, the others are copies of it.
+  struct Deal {                            // of the units of one class onto the queues [q_lo, q_lo + n_homes * load.size())
+    int32_t q_lo = 0, n_homes = 1;
+    std::vector<double> load;              // of the queues of one home
+    std::vector<std::vector<std::pair<int32_t, int32_t>>> units;   // per queue of a home: (item, n-th head group of the home)
+  };
   struct Schedule {
     std::vector<WorkItem> items;
     std::vector<MergeItem> merges;
     std::vector<double> item_cost;
-    std::vector<std::vector<int32_t>> queues;   // flat (item, group) pairs
-    std::vector<double> load;
+    Deal deal[2];                               // of the other tiles' units, of the window tiles'
     int32_t n_slots = 0, n_queues = 0, lse_queue0 = 0;
     double dealt_end = 0, end = 0;              // predicted, of the last queue, before and after the refinement
   };
@@ -307,98 +314,88 @@ void build_plan(purekv_plan& p, int n_cu) {
       s.item_cost.push_back(c);
     }
   };
-  // Units are dealt longest first, each to the least-loaded queue that may run it.  Workgroup q runs on XCD q % 8
-  // (round-robin dispatch); when the head counts allow it, the units of one KV head stay on a fixed set of XCDs so
-  // that each L2 holds the K/V of few KV heads.  Queues [0, lse_queue0) hold the units of the other tiles, [lse_queue0,
-  // n_queues) those of the window tiles; a plan without a window keeps one class: every workgroup keeps the exact sum when
-  // the log-sum-exp is asked for.
+  // Units are dealt longest first, each to the least-loaded queue that may run it.  Queues [0, lse_queue0) hold the units of
+  // the other tiles, [lse_queue0, n_queues) those of the window tiles; a plan without a window keeps one class: every
+  // workgroup keeps the exact sum when the log-sum-exp is asked for.
   auto item_class = [&](const Schedule& s, size_t it) { return s.lse_queue0 > 0 && window_tile(s.items[it].qtile) ? 1 : 0; };
-  auto affine = [&](const Schedule& s, int32_t q_lo, int32_t q_hi) {
+  auto homes_of = [&](const Schedule& s, int32_t n) {
     // (not for a head subset: its KV heads may be few, and every queue has to receive a unit; and only with the same number
-    // of queues for every KV head inside the range: the sets of a divided plan are sized for that)
-    return p.head_sel.empty() && s.n_queues % 8 == 0 && (g.Hkv % 8 == 0 || 8 % g.Hkv == 0) && (q_hi - q_lo) % affinity_groups == 0;
+    // of queues for every KV head: the sets of a divided plan are sized for that)
+    const int32_t homes = std::min(g.Hkv, 8);
+    return p.head_sel.empty() && s.n_queues % 8 == 0 && (g.Hkv % 8 == 0 || 8 % g.Hkv == 0) && n % homes == 0 ? homes : 1;
   };
-  auto home_of_queue = [&](int32_t q) { return g.Hkv >= 8 ? q % 8 : q % 8 % g.Hkv; };
-  auto home_of_group = [&](int32_t grp) { return g.Hkv >= 8 ? grp * g.Gs / g.G % 8 : grp * g.Gs / g.G; };
-  auto deal_class = [&](Schedule& s, int cls, int32_t q_lo, int32_t q_hi, bool loads_only) {
-    const bool aff = affine(s, q_lo, q_hi);
+  // Head groups of home `home` of n_homes, ascending (without homes: every selected group).
+  auto groups_of_home = [&](int32_t n_homes, int32_t home) {
+    std::vector<int32_t> groups;
+    for (int32_t grp = 0; grp < g.n_groups; ++grp)
+      if (group_selected(grp) && grp * g.Gs / g.G % n_homes == home % n_homes) groups.push_back(grp);
+    return groups;
+  };
+  auto deal_class = [&](const Schedule& s, int cls, int32_t q_lo, int32_t q_hi, bool loads_only) {
+    Deal d;
+    d.q_lo = q_lo;
+    d.n_homes = homes_of(s, q_hi - q_lo);
+    const int32_t n = (q_hi - q_lo) / d.n_homes, n_groups_home = n_groups_sel / d.n_homes;
+    d.load.assign(n, 0.0);
+    if (!loads_only) d.units.resize(n);
     typedef std::pair<double, int32_t> LoadQueue;   // least loaded first, then lowest index
-    std::vector<std::priority_queue<LoadQueue, std::vector<LoadQueue>, std::greater<LoadQueue>>> by_home(aff ? 8 : 1);
-    for (int32_t q = q_lo; q < q_hi; ++q) by_home[aff ? home_of_queue(q) : 0].push({0.0, q});
+    std::vector<LoadQueue> idle(n);
+    for (int32_t q = 0; q < n; ++q) idle[q] = {0.0, q};
+    std::priority_queue<LoadQueue, std::vector<LoadQueue>, std::greater<LoadQueue>> heap(std::greater<LoadQueue>(), std::move(idle));
     for (size_t it = 0; it < s.items.size(); ++it) {
       if (item_class(s, it) != cls) continue;
-      for (int32_t grp = 0; grp < g.n_groups; ++grp) {
-        if (!group_selected(grp)) continue;
-        auto& heap = by_home[aff ? home_of_group(grp) : 0];
+      for (int32_t i = 0; i < n_groups_home; ++i) {
         LoadQueue lq = heap.top();
         heap.pop();
-        if (!loads_only) {
-          s.queues[lq.second].push_back(static_cast<int32_t>(it));
-          s.queues[lq.second].push_back(grp);
-        }
-        lq.first = s.load[lq.second] += s.item_cost[it];
+        if (!loads_only) d.units[lq.second].emplace_back(static_cast<int32_t>(it), i);
+        lq.first = d.load[lq.second] += s.item_cost[it];
         heap.push(lq);
       }
     }
+    return d;
   };
-  // Refinement: while it lowers the larger of the two loads, move a unit from the fullest queue to another queue that may
-  // run it, or exchange a unit of each.
-  auto refine_class = [&](Schedule& s, int32_t q_lo, int32_t q_hi) {
-    const bool aff = affine(s, q_lo, q_hi);
-    auto& queues = s.queues;
-    auto& load = s.load;
-    auto allowed = [&](int32_t q, int32_t grp) { return !aff || home_of_queue(q) == home_of_group(grp); };
-    for (int32_t round = 0; round < 8 * (q_hi - q_lo); ++round) {
-      const int32_t qa = static_cast<int32_t>(std::max_element(load.begin() + q_lo, load.begin() + q_hi) - load.begin());
+  // Refinement: while it lowers the larger of the two loads, move a unit from the fullest queue to another one, or exchange a
+  // unit of each.
+  auto refine = [](const Schedule& s, Deal& d) {
+    const int32_t n = static_cast<int32_t>(d.load.size());
+    auto& load = d.load;
+    for (int32_t round = 0; round < 8 * n; ++round) {
+      const int32_t qa = static_cast<int32_t>(std::max_element(load.begin(), load.end()) - load.begin());
+      auto& ua = d.units[qa];
       double best_gain = 1e-9;
       int32_t best_q = -1;
       size_t best_u = 0, best_v = SIZE_MAX;
-      for (size_t u = 0; u + 1 < queues[qa].size(); u += 2) {
-        const double cu = s.item_cost[queues[qa][u]];
-        bool seen = false;   // a unit of the same cost that may go to the same queues
-        for (size_t x = 0; x < u && !seen; x += 2)
-          seen = s.item_cost[queues[qa][x]] == cu && (!aff || home_of_group(queues[qa][x + 1]) == home_of_group(queues[qa][u + 1]));
+      for (size_t u = 0; u < ua.size(); ++u) {
+        const double cu = s.item_cost[ua[u].first];
+        bool seen = false;   // a unit of the same cost
+        for (size_t x = 0; x < u && !seen; ++x) seen = s.item_cost[ua[x].first] == cu;
         if (seen) continue;
-        for (int32_t qb = q_lo; qb < q_hi; ++qb) {
-          if (0.5 * (load[qa] - load[qb]) <= best_gain || !allowed(qb, queues[qa][u + 1])) continue;   // (no larger gain there)
+        for (int32_t qb = 0; qb < n; ++qb) {
+          if (0.5 * (load[qa] - load[qb]) <= best_gain) continue;   // (no larger gain there)
           // move u: new pair maximum = max(load[qa] - cu, load[qb] + cu)
           double gain = load[qa] - std::max(load[qa] - cu, load[qb] + cu);
-          if (gain > best_gain) {
-            best_gain = gain;
-            best_q = qb;
-            best_u = u;
-            best_v = SIZE_MAX;
-          }
-          for (size_t v = 0; v + 1 < queues[qb].size(); v += 2) {
-            const double cv = s.item_cost[queues[qb][v]];
-            if (cv >= cu || !allowed(qa, queues[qb][v + 1])) continue;
+          if (gain > best_gain) best_gain = gain, best_q = qb, best_u = u, best_v = SIZE_MAX;
+          for (size_t v = 0; v < d.units[qb].size(); ++v) {
+            const double cv = s.item_cost[d.units[qb][v].first];
+            if (cv >= cu) continue;
             gain = load[qa] - std::max(load[qa] - cu + cv, load[qb] + cu - cv);
-            if (gain > best_gain) {
-              best_gain = gain;
-              best_q = qb;
-              best_u = u;
-              best_v = v;
-            }
+            if (gain > best_gain) best_gain = gain, best_q = qb, best_u = u, best_v = v;
           }
         }
       }
       if (best_q < 0) break;
-      const int32_t ui = queues[qa][best_u], ug = queues[qa][best_u + 1];
+      auto& ub = d.units[best_q];
+      const double cu = s.item_cost[ua[best_u].first];
+      double moved = cu;
       if (best_v == SIZE_MAX) {
-        queues[qa].erase(queues[qa].begin() + best_u, queues[qa].begin() + best_u + 2);
-        queues[best_q].push_back(ui);
-        queues[best_q].push_back(ug);
-        load[qa] -= s.item_cost[ui];
-        load[best_q] += s.item_cost[ui];
+        ub.push_back(ua[best_u]);
+        ua.erase(ua.begin() + best_u);
       } else {
-        const int32_t vi = queues[best_q][best_v], vg = queues[best_q][best_v + 1];
-        queues[qa][best_u] = vi;
-        queues[qa][best_u + 1] = vg;
-        queues[best_q][best_v] = ui;
-        queues[best_q][best_v + 1] = ug;
-        load[qa] += s.item_cost[vi] - s.item_cost[ui];
-        load[best_q] += s.item_cost[ui] - s.item_cost[vi];
+        moved -= s.item_cost[ub[best_v].first];
+        std::swap(ua[best_u], ub[best_v]);
       }
+      load[qa] -= moved;
+      load[best_q] += moved;
     }
   };
   // `limit`: a schedule whose queues end no sooner on average, or whose longest unit does not, is given up undealt.
@@ -421,19 +418,17 @@ void build_plan(purekv_plan& p, int n_cu) {
     s.end = std::max(sum[0] / q_split, longest[0]);
     if (q_split < s.n_queues) s.end = std::max(s.end, kExactSumCost * std::max(sum[1] / (s.n_queues - q_split), longest[1]));
     if (s.end >= limit) return s;
-    if (!loads_only) s.queues.resize(s.n_queues);
-    s.load.assign(s.n_queues, 0.0);
     auto last_end = [&]() {
-      double end = 0;
-      for (int32_t q = 0; q < s.n_queues; ++q) end = std::max(end, s.load[q] * (q >= q_split ? kExactSumCost : 1.0));
+      double end = *std::max_element(s.deal[0].load.begin(), s.deal[0].load.end());
+      if (!s.deal[1].load.empty())
+        end = std::max(end, kExactSumCost * *std::max_element(s.deal[1].load.begin(), s.deal[1].load.end()));
       return end;
     };
-    if (q_split < s.n_queues) deal_class(s, 1, q_split, s.n_queues, loads_only);
-    deal_class(s, 0, 0, q_split, loads_only);
+    if (q_split < s.n_queues) s.deal[1] = deal_class(s, 1, q_split, s.n_queues, loads_only);
+    s.deal[0] = deal_class(s, 0, 0, q_split, loads_only);
     s.dealt_end = s.end = last_end();
     if (loads_only) return s;
-    if (q_split < s.n_queues) refine_class(s, q_split, s.n_queues);
-    refine_class(s, 0, q_split);
+    for (Deal& d : s.deal) refine(s, d);
     s.end = last_end();
     return s;
   };
@@ -444,10 +439,11 @@ void build_plan(purekv_plan& p, int n_cu) {
   // 25.0; sparse, 55 of 24 x 8 + 264, 8/8 of 128: 75.3 -> 61.1; 6 of 22 x 19 + 22, 28/4 of 64: 32.5 -> 26.5; 66 drawn shapes 0.97
   // in the mean, at most 1.04.
   // Plans with more than three units per workgroup balance with any of them and take 0.8 without a search, as do those whose
-  // first schedule ends within 3 % of the average load of uncut lists.  The search deals loads only, 0.05 ms a factor, and
-  // no schedule that the one in hand beats on the average already; the one it finds is dealt in full and refined like the
-  // first.  Planning 32 shapes, one length always -> with the search: 23.4 -> 19.3 ms in all (heaps pay for it); sparse, 64
-  // frames of 16 x 16, 5.7 -> 2.1; dense window plan, 8 frames of 24 x 24 + 128, 32/8 heads, 0.39 -> 0.72.
+  // first schedule ends within 3 % of the average load of uncut lists.  The search deals loads only, and no schedule that the
+  // one in hand beats on the average already; the one it finds is dealt in full and refined like the first.  Planning 178
+  // shapes (170 drawn), one length always -> all homes dealt, with the search -> one home, with the search: 184 -> 142 -> 95 ms
+  // in all; dense window plan, 8 frames of 24 x 24 + 128, 32/8 heads, 0.37 -> 0.62 -> 0.20; sparse, 64 frames of 16 x 16 + 256,
+  // 28/4 heads, 5.6 -> 2.0 -> 1.3; dense, 128 frames, 18 -> 14 -> 13 (its lists and steps, not the schedule).
   constexpr double kSliceFactor = 0.8, kOtherFactors[] = {0.4, 0.55, 0.65, 1.0, 1.25, 1.6, 1e9}, kSooner = 1.03;
   const double kNoLimit = std::numeric_limits<double>::infinity();
   Schedule chosen = make(kSliceFactor, window_sets[0], false, kNoLimit);
@@ -472,7 +468,18 @@ void build_plan(purekv_plan& p, int n_cu) {
   p.n_slots = chosen.n_slots;
   p.n_queues = chosen.n_queues;
   p.lse_queue0 = chosen.lse_queue0;
-  std::vector<std::vector<int32_t>>& queues = chosen.queues;
+  std::vector<std::vector<int32_t>> queues(p.n_queues);   // flat (item, group) pairs
+  for (const Deal& d : chosen.deal)
+    for (int32_t home = 0; home < d.n_homes && !d.load.empty(); ++home) {
+      // queues of home x: q % n_homes == x
+      const std::vector<int32_t> groups = groups_of_home(d.n_homes, d.q_lo + home);
+      for (size_t i = 0; i < d.units.size(); ++i)
+        for (const auto& u : d.units[i]) {
+          auto& queue = queues[d.q_lo + home + d.n_homes * static_cast<int32_t>(i)];
+          queue.push_back(u.first);
+          queue.push_back(groups[u.second]);
+        }
+    }
   // Order within a queue: slices of split lists first, except the closing slice of a list, which goes last (when it
   // ends, the other slices of its list, run first elsewhere, have normally long arrived: the workgroup that the
   // cost model charged for combining them is then the one that does); whole lists in between, longest first (item
