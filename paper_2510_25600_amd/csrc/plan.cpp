@@ -178,14 +178,19 @@ void build_plan(purekv_plan& p, int n_cu) {
   }
 
   // ---- cost model, in steps of one plain tile ----
-  // From the cycles of the workgroups of 22 shapes against what they ran: a half skipped saves MFMAs but no time, a step with
-  // the full predicate takes a tenth more; a unit (rows written, state reset, query rows fetched) as much as a step, 1.4
-  // with several heads of 128 stacked; a slice 1 more (fp32 rows through to memory, acknowledged) and, at the end of its
-  // queue, 1.5 for the look whether its list is complete; the workgroup that runs a list's closing slice, last in its queue,
-  // then combines it (2 us and 2 us a slice of 256 rows x 128: one CU reads them all).
-  constexpr double kGeneralCost = 1.1, kSliceCost = 2.5;
-  const double kUnitCost = g.Gs > 1 && g.d == 128 ? 1.4 : 1.0;
-  auto combine_cost = [&](int32_t n_slices) { return g.d == 128 ? 1.3 + 1.4 * n_slices : 1.0 + 0.7 * n_slices; };
+  // Fitted to the cycles of the workgroups of 60 shapes of both patterns and head widths, with 1 to 8 stacked heads, against
+  // what they ran.  A half skipped saves MFMAs but no time; a step with the full predicate takes 0.2 to 0.5 more.  A unit (rows
+  // written, state reset, query rows fetched) takes 1.2, with several heads stacked 1.4 under the dense pattern and more
+  // where masked steps lie around the switch.  A slice takes 3.5 to 6 more (tiles that nobody else reads meanwhile, fp32 rows
+  // through to memory, acknowledged, the look whether its list is complete), and the workgroup that runs a list's closing
+  // slice, last in its queue, combines the list: 5 more for three slices of 256 rows x 128.  Workgroups that run slices get
+  // that much less besides: with 2.5 for a slice and 1.4 for every stacked unit, the sparse plan of 8 frames of 24 x 24 + 128
+  // tokens, 32/8 heads, ended with closing workgroups of 153 thousand cycles (mean 131).  With these figures its prefill takes
+  // 0.977 of that, 13 frames of 17 x 19 + 45, 28/4 heads, 0.87; 630 drawn shapes 0.979 in the mean.
+  constexpr double kGeneralCost = 1.3, kSliceCost = 5.0;
+  const bool dense = g.pattern == PUREKV_PATTERN_DENSE;
+  const double kUnitCost = g.Gs == 1 ? 1.2 : dense ? 1.4 : g.d == 128 ? 1.7 : 2.1;
+  auto combine_cost = [&](int32_t n_slices) { return 2.5 + 0.7 * n_slices; };
   std::vector<double> cost_before(p.tiles.size() + 1, 0.0);   // of the tiles before, in list order
   for (size_t i = 0; i < p.tiles.size(); ++i) {
     const TileRef& t = p.tiles[i];

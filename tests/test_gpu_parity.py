@@ -238,7 +238,7 @@ def test_prefill_reference_is_raised(pattern, d, step):
 
 
 @pytest.mark.parametrize("pattern", [0, 3])
-@pytest.mark.parametrize("frames,patch_h,patch_w,text,dim", [(3, 9, 11, 700, 128), (2, 16, 16, 600, 64)])
+@pytest.mark.parametrize("frames,patch_h,patch_w,text,dim", [(4, 9, 11, 700, 128), (2, 16, 16, 600, 64)])
 def test_prefill_rows_whose_scores_are_all_minus_infinity(frames, patch_h, patch_w, text, dim, pattern):
     """A row none of whose scores is finite has no weights: its output is 0 and its log-sum-exp -inf, whether its key list
     is run whole or in slices; and a slice without a finite score adds nothing to the others."""

@@ -360,6 +360,26 @@ def test_plans_of_searched_slice_lengths(shape, heads, dim, pattern, window, n_w
     _check_plan_against_oracle(F, ph, pw, T, heads[0], heads[1], dim, pattern, n_wg=n_wg, window=window)
 
 
+@pytest.mark.parametrize("shape,heads", [((8, 24, 24, 128), (32, 8)), ((13, 17, 19, 45), (28, 4))])
+def test_workgroups_that_run_slices_get_less_besides(shape, heads):
+    """Sparse plans whose text rows' lists are cut, by what the parts of a workgroup's work were measured to take (in steps of a
+    plain tile: a step with the full predicate 1.3, a unit 1.7, a slice 5 and the combination 2.5 + 0.7 a slice more): the
+    last workgroup ends near the mean, also if it runs slices."""
+    plan = pk.Plan(*shape, *heads, 128, 3, host_only=True)
+    c = plan.counts()
+    items = [plan.item(i) for i in range(c["n_items"])]
+    assert any(it[4] > 1 for it in items)
+    ends = []
+    for q in range(c["n_workgroups"]):
+        end = sum(1.3 if k & (k >> 1) & 0x55555555 else 1.0 for _, _, k, _ in plan.steps(q))
+        for i, _ in plan.queue(q):
+            split, n_splits = items[i][3], items[i][4]
+            end += 1.7 + (5.0 if n_splits > 1 else 0.0) + (2.5 + 0.7 * n_splits if 1 < n_splits == split + 1 else 0.0)
+        ends.append(end)
+    assert max(ends) <= 1.12 * np.mean(ends)
+    plan.close()
+
+
 def test_searching_a_schedule_costs_little_beside_listing_the_tiles():
     """A low layer that is searched on 256 workgroups, against the same lists dealt to 16, where nothing is searched (37 units
     a workgroup): at most twice the time, the least of many tries of each in turn."""
