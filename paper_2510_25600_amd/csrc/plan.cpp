@@ -201,9 +201,9 @@ void build_plan(purekv_plan& p, int n_cu) {
 
   // ---- window plans: the query tiles whose rows want the log-sum-exp get workgroups of their own ----
   // Only the last lse_rows rows are asked for their log-sum-exp (the recent window of Eq. 2).  Keeping the exact row
-  // sum costs the tile loop 7-10 % (two more vector instructions per pair of scores), so the query tiles that
-  // hold such rows ("window tiles") are dealt to a set of workgroups of their own, sized by their share of the work,
-  // and only those workgroups run the variant of the loop that keeps the sum.  A set of few workgroups needs units
+  // sum costs a step 7 % with heads of 128, 9 % with heads of 64 (two more vector instructions per pair of scores), so the
+  // query tiles that hold such rows ("window tiles") are dealt to a set of workgroups of their own, sized by their share of
+  // the work, and only those workgroups run the variant of the loop that keeps the sum.  A set of few workgroups needs units
   // small enough to be balanced over it: the window tiles' lists are cut into the number of slices that minimises an
   // estimate of the set's longest queue (equal units dealt evenly, the combination charged to the queue that closes a
   // list), and the set is made large enough not to be the last to finish.
@@ -213,7 +213,10 @@ void build_plan(purekv_plan& p, int n_cu) {
   auto window_tile = [&](int32_t qt) {
     return p.lse_rows > 0 && int64_t(qt + 1) * rows_per_qtile > int64_t(g.N) - p.lse_rows;
   };
-  constexpr double kExactSumCost = 1.10;   // of a step that keeps the exact sum
+  // Of a step that keeps the exact sum.  The cycles of every workgroup with the sum against those of the same plan without it:
+  // median 1.070 and 1.085 over dense plans of 19 to 274 steps a workgroup (a launch as a whole differs by 2 to 7 %: units and
+  // slices cost the same, and the clock is a little higher).
+  const double kExactSumCost = g.d == 128 ? 1.07 : 1.09;
   struct WindowSet {
     int32_t n_queues, slices;
   };

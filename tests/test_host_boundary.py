@@ -338,6 +338,20 @@ def test_window_plan_of_the_benchmark_low_layer_is_divided():
     plan.close()
 
 
+def test_window_tiles_that_take_just_less_than_a_quarter_of_the_launch_are_set_apart():
+    """With heads of 128 a step that keeps the exact row sum takes 1.07 of one that does not: of the low layer of 25 frames of
+    11 x 8 + 241 tokens, 32/8 heads, the window's tiles are then less than a quarter, the largest share that is set apart (at
+    1.10 they would be more)."""
+    plan = pk.Plan(25, 11, 8, 241, 32, 8, 128, 0, host_only=True, lse_window=241)
+    c = plan.counts()
+    lens = [len(plan.qtile_list(qt)) for qt in range(c["n_qtiles"])]
+    rows = 32 * c["row_blocks"]
+    window = sum(x for qt, x in enumerate(lens) if (qt + 1) * rows > c["N"] - 241)
+    share = [cost * window / (cost * window + sum(lens) - window) for cost in (1.07, 1.10)]
+    assert share[0] < 0.25 < share[1] and c["lse_queue0"] > 0
+    plan.close()
+
+
 @pytest.mark.parametrize("window", [1, 19, 32, 200, 233])
 @pytest.mark.parametrize("pattern", [0, 3])
 @pytest.mark.parametrize("shape", [(4, 8, 8, 32), (3, 5, 7, 19), (5, 16, 16, 200), (40, 16, 16, 64)])
