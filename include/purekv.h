@@ -167,11 +167,13 @@ PUREKV_API int purekv_plan_item(const purekv_plan_t* plan, int32_t it, int32_t i
 PUREKV_API int purekv_plan_queue(const purekv_plan_t* plan, int32_t wg, int32_t* units, int32_t cap);
 /* Copies the steps of persistent workgroup `wg`, in execution order, into steps[0 .. 4*cap): one record of four
  * values per step: {byte offset of the key tile's first row in K and V, need bits | last << 16 | first << 17 |
- * (rows of the tile that exist - 1) << 18 | owner << 24, kind bits, first key of the tile}.  A step stages one key
+ * (rows of the tile that exist - 1) << 18 | owner << 24 | plain << 25 | fetch << 26, kind bits, first key of the tile}.  A step stages one key
  * tile of its unit's list (Sec. 3.2: the lists are the pattern's block indices); `first` / `last` mark the ends of a
  * unit, units follow each other in the order purekv_plan_queue reports; `owner` marks the one step of the launch
- * that also emits the squared norms of the tile's V rows.  Returns the number of steps (may exceed cap) or a
- * negative status. */
+ * that also emits the squared norms of the tile's V rows; `plain` marks the steps of which every row block with rows
+ * needs both halves in full (run without a look at need and kinds), `fetch` the one step of every unit but a workgroup's
+ * last during which the next unit's query rows are requested (the last step but one, or the only one).  Returns the
+ * number of steps (may exceed cap) or a negative status. */
 PUREKV_API int purekv_plan_steps(const purekv_plan_t* plan, int32_t wg, int32_t* steps, int32_t cap);
 
 /* Spearman's rank correlation between two score arrays, row by row (Sec. 3.3, Eq. 5-7: the check that the scores

@@ -208,7 +208,7 @@ int purekv_plan_qtile_list(const purekv_plan_t* p, int32_t qt, int32_t* refs, in
   const int32_t b = p->qtile_begin[qt], len = p->qtile_begin[qt + 1] - b;
   for (int32_t i = 0; i < len && i < cap; ++i) {
     refs[3 * i] = p->tiles[b + i].tile;
-    refs[3 * i + 1] = (int32_t)(p->tiles[b + i].need & kStepPublic);
+    refs[3 * i + 1] = (int32_t)(p->tiles[b + i].need & ~kStepPlain);
     refs[3 * i + 2] = (int32_t)p->tiles[b + i].kinds;
   }
   return len;
@@ -229,7 +229,7 @@ int purekv_plan_steps(const purekv_plan_t* p, int32_t wg, int32_t* steps, int32_
   const int32_t b = p->queue_begin[wg], len = p->queue_begin[wg + 1] - b;
   for (int32_t i = 0; i < len && i < cap; ++i) {
     const StreamEntry& e = p->stream[b + i];
-    const int32_t rec[4] = {(int32_t)e.kv_off, (int32_t)(e.need & kStepPublic), (int32_t)e.kinds, e.k0};
+    const int32_t rec[4] = {(int32_t)e.kv_off, (int32_t)e.need, (int32_t)e.kinds, e.k0};
     for (int k = 0; k < 4; ++k) steps[4 * i + k] = rec[k];
   }
   return len;

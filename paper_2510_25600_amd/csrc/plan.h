@@ -59,12 +59,11 @@ struct StreamEntry {
   int32_t k0;          // first key of the tile
 };
 
-// Bits of StreamEntry::need that spare the kernel's loop its own tests (not part of the records that inspection calls return).
+// Bits of StreamEntry::need that spare the kernel's loop its own tests.
 constexpr uint32_t kStepLast = 1u << 16, kStepFirst = 1u << 17, kStepOwner = 1u << 24;
 constexpr uint32_t kStepPlain = 1u << 25;   // every row block that has rows needs both halves of the tile, without a mask
 constexpr uint32_t kStepFetchQ = 1u << 26;  // the query rows of the workgroup's next unit are requested during this step:
                                             // the last but one of its unit (the only one of a unit of one step)
-constexpr uint32_t kStepPublic = kStepPlain - 1u;
 
 // A unit = work item x group of stacked query heads, run by one workgroup from its first to its last stream entry.
 struct Unit {

@@ -260,16 +260,20 @@ def _check_plan_against_oracle(F, ph, pw, T, hq, hkv, d, pattern, n_wg=256, wind
 def _check_steps_against_lists(plan, c, items, hq, hkv, d, n, R, gs, kv_strides=None):
     """The steps a workgroup executes against the lists they were made from: every unit runs, once and in order, the
     tiles of its slice of its query tile's list, with the addresses, first/last marks and row counts the kernel relies
-    on, and every (KV head, key tile) has exactly one owner step."""
+    on, and every (KV head, key tile) has exactly one owner step.  The marks that the kernel takes the place of tests of its
+    own: a step is plain exactly when every row block that has rows needs both halves of the tile in full, and every unit but
+    a workgroup's last requests the next one's query rows once, in its last step but one (or its only one)."""
     g = hq // hkv
     kv_sh, kv_st = kv_strides if kv_strides else (n * d, d)
     owners = set()
     for q in range(c["n_workgroups"]):
         steps = plan.steps(q)
         pos = 0
-        for it, head0 in plan.queue(q):
+        queue = plan.queue(q)
+        for u, (it, head0) in enumerate(queue):
             qt, lb, nt, sp, ns, slot = items[it]
             kvh = head0 // g
+            need_all = sum(3 << 2 * rb for rb in range(R) if (qt * R + rb) * pk.BLOCK < n)
             first_pos = lb - _list_begin(plan, c, qt)
             want = plan.qtile_list(qt)[first_pos:first_pos + nt]
             for i, (t, need, kinds) in enumerate(want):
@@ -278,6 +282,9 @@ def _check_steps_against_lists(plan, c, items, hq, hkv, d, n, R, gs, kv_strides=
                 assert flags & 0xFFFF == need and got_kinds == kinds
                 assert (flags >> 17) & 1 == (i == 0) and (flags >> 16) & 1 == (i == nt - 1)
                 assert ((flags >> 18) & 63) + 1 == min(pk.BK, n - k0)
+                assert (flags >> 25) & 1 == (need == need_all and kinds == 0)
+                assert (flags >> 26) & 1 == (u + 1 < len(queue) and i == max(nt - 2, 0))
+                assert flags >> 27 == 0
                 if (flags >> 24) & 1:
                     assert (kvh, t) not in owners
                     owners.add((kvh, t))
