@@ -376,7 +376,7 @@ def test_window_plans_small(shape, pattern, window):
                                              ((6, 22, 19, 40), (28, 4), 64), ((5, 8, 8, 40), (24, 8), 128)])
 def test_plans_of_searched_slice_lengths(shape, heads, dim, pattern, window, n_wg):
     """At most three units per workgroup: the planner tries other slice lengths and sizes of the window set, also where the
-    workgroups (250) do not divide among the XCDs."""
+    workgroups (250) do not divide among the XCDs.  (Which shapes then take another one: the test below.)"""
     F, ph, pw, T = shape
     _check_plan_against_oracle(F, ph, pw, T, heads[0], heads[1], dim, pattern, n_wg=n_wg, window=window)
 
@@ -399,6 +399,30 @@ def test_workgroups_that_run_slices_get_less_besides(shape, heads):
         ends.append(end)
     assert max(ends) <= 1.12 * np.mean(ends)
     plan.close()
+
+
+@pytest.mark.parametrize("shape,heads,dim,pattern,window,longer,lse_queue0", [
+    ((2, 18, 22, 200), (24, 8), 64, 0, 0, True, 0),           # whole lists
+    ((9, 15, 21, 93), (24, 8), 64, 0, 0, True, 0),
+    ((8, 11, 9, 40), (28, 4), 128, 0, 40, True, 0),
+    ((15, 14, 16, 93), (16, 2), 128, 0, 0, False, 0),
+    ((17, 10, 18, 128), (28, 4), 64, 3, 0, False, 0),
+    ((7, 21, 20, 40), (24, 8), 64, 0, 40, True, 208),         # the estimate alone sets 72 workgroups apart, from 184 on
+    ((15, 10, 14, 200), (32, 8), 128, 0, 200, True, 192)])    # 96, from 160 on
+def test_another_slice_length_or_window_set_is_taken(shape, heads, dim, pattern, window, longer, lse_queue0):
+    """Shapes that end sooner with slices of another length than 0.8 of a workgroup's average load (longer ones, or shorter), or
+    with another size of the window set than the estimate's."""
+    plan = pk.Plan(*shape, *heads, dim, pattern, host_only=True, lse_window=window)
+    c = plan.counts()
+    chunk = max(8, int(0.8 * c["n_tile_refs"] * c["n_head_groups"] / 256 + 0.5))
+    rest = [qt for qt in range(c["n_qtiles"])
+            if not (c["lse_queue0"] and (qt + 1) * 32 * c["row_blocks"] > c["N"] - window)]   # window tiles have their own rule
+    lens = {qt: len(plan.qtile_list(qt)) for qt in rest}
+    usual = sum(-(-x // chunk) if 2 * x > 3 * chunk else 1 for x in lens.values())
+    items = sum(plan.item(i)[0] in lens for i in range(c["n_items"]))
+    assert (items < usual if longer else items > usual) and c["lse_queue0"] == lse_queue0
+    plan.close()
+    _check_plan_against_oracle(*shape, *heads, dim, pattern, window=window)
 
 
 def test_searching_a_schedule_costs_little_beside_listing_the_tiles():
