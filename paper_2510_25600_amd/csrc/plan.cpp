@@ -186,7 +186,7 @@ void build_plan(purekv_plan& p, int n_cu) {
   // slice, last in its queue, combines the list: 5 more for three slices of 256 rows x 128.  Workgroups that run slices get
   // that much less besides: with 2.5 for a slice and 1.4 for every stacked unit, the sparse plan of 8 frames of 24 x 24 + 128
   // tokens, 32/8 heads, ended with closing workgroups of 153 thousand cycles (mean 131).  With these figures its prefill takes
-  // 0.977 of that, 13 frames of 17 x 19 + 45, 28/4 heads, 0.87; 630 drawn shapes 0.979 in the mean.
+  // 0.98 of that, 13 frames of 17 x 19 + 45, 28/4 heads, 0.87; 300 drawn shapes 0.978 in the mean, at most 1.07.
   constexpr double kGeneralCost = 1.3, kSliceCost = 5.0;
   const bool dense = g.pattern == PUREKV_PATTERN_DENSE;
   const double kUnitCost = g.Gs == 1 ? 1.2 : dense ? 1.4 : g.d == 128 ? 1.7 : 2.1;
@@ -442,10 +442,10 @@ void build_plan(purekv_plan& p, int n_cu) {
   };
   // Slice lengths, as factors of the average load of a workgroup.  None suits all: whole lists leave a shape with few units
   // per workgroup with a long tail, short slices cost unit switches and combinations.  0.8 unless another one ends 3 %
-  // sooner by the model, whose workgroups' ends scatter by as much.  Prefill alone, always 0.8 and the model before it -> this:
+  // sooner by the model, whose workgroups' ends scatter by as much.  Prefill alone, always 0.8 -> this, with the costs of its day:
   // dense, 14 frames of 19 x 8 patches + 51 tokens, 28/4 heads of 128: 65.2 -> 53.7 us; 11 of 22 x 11 + 10, 8/8 of 64: 33.7 ->
   // 25.0; sparse, 55 of 24 x 8 + 264, 8/8 of 128: 75.3 -> 61.1; 6 of 22 x 19 + 22, 28/4 of 64: 32.5 -> 26.5; 66 drawn shapes 0.97
-  // in the mean, at most 1.04.
+  // in the mean.
   // Plans with more than three units per workgroup balance with any of them and take 0.8 without a search, as do those whose
   // first schedule ends within 3 % of the average load of uncut lists.  The search deals loads only, and no schedule that the
   // one in hand beats on the average already; the one it finds is dealt in full and refined like the first.  Planning 178
