@@ -28,11 +28,12 @@
  *   - Return value: PUREKV_OK (0) or a negative purekv_status.  All argument validation happens on the
  *     host before any GPU call, so EINVAL / EUNSUPPORTED / EWORKSPACE never leave work half enqueued.
  *   - Workspaces: purekv_workspace_bytes() gives the size an operation needs; pass a device buffer of at
- *     least that size (may be NULL when the size is 0), 256-byte aligned.  The PREFILL and DECODE workspaces begin
- *     with arrival counters through which workgroups of one launch hand partial results to each other: such a
- *     buffer must be initialised ONCE with purekv_workspace_init before its first use (and again after a failed
- *     launch, or after anything else wrote to it); every call leaves it ready for the next.  Calls that may overlap
- *     on the GPU need workspaces of their own; a plan may be shared by any number of streams.
+ *     least that size (may be NULL when the size is 0), 256-byte aligned.  Workgroups of one launch hand partial
+ *     results to each other through arrival counters at the head of the PREFILL workspace, and through counters and
+ *     the DECODE workspace itself, all of which is zero between calls: such a buffer must be initialised ONCE with
+ *     purekv_workspace_init before its first use (and again after a failed launch, or after anything else wrote to
+ *     it); every call leaves it ready for the next.  Calls that may overlap on the GPU need workspaces of their own; a
+ *     plan may be shared by any number of streams.
  */
 #ifndef PUREKV_H_
 #define PUREKV_H_
@@ -196,8 +197,8 @@ PUREKV_API int purekv_spearman(const float* s_hat, const float* s, int32_t n_row
  * decode stage.  IMPORTANCE (Eq. 2) and COMPACT need none. */
 PUREKV_API size_t purekv_workspace_bytes(const purekv_plan_t* plan, int op, int32_t n_layers, int32_t w, int32_t cap);
 /* Prepares a fresh workspace of `op` (same n_layers, w, cap as for purekv_workspace_bytes): clears the arrival
- * counters of a PREFILL or DECODE workspace with a small kernel on `stream` (no memset node: the call may be
- * captured in a graph); nothing to do for the other ops.  EWORKSPACE if ws is NULL or too small while the op needs
+ * counters of a PREFILL workspace, or all ws_bytes of a DECODE workspace, with a small kernel on `stream` (no memset
+ * node: the call may be captured in a graph); nothing to do for the other ops.  EWORKSPACE if ws is NULL or too small while the op needs
  * one. */
 PUREKV_API int purekv_workspace_init(const purekv_plan_t* plan, int op, void* ws, size_t ws_bytes, int32_t n_layers,
                                      int32_t w, int32_t cap, void* stream);
@@ -300,13 +301,17 @@ PUREKV_API int purekv_decode_attn(const purekv_plan_t* plan, const void* q_new, 
  * One decode step in one launch (the decode stage of the paper's inference-speed table, per generated token):
  * stores k_new, v_new [Hkv, d] as row n_cached of kc, vc (as purekv_kv_append does) and attends q_new over rows
  * 0 .. n_cached inclusive (as purekv_decode_attn with n_cached + 1 does).  0 <= n_cached < cap.
- * Both decode calls count chunk arrivals in their workspace (see "Workspaces" above): calls on different
+ * Both decode calls hand partial results over in their workspace (see "Workspaces" above): calls on different
  * workspaces are independent, whether or not they share a plan.
  */
 PUREKV_API int purekv_decode_step(const purekv_plan_t* plan, const void* q_new, const void* k_new, const void* v_new,
                                   void* kc, void* vc, int32_t n_cached, int32_t cap, void* out, void* ws,
                                   size_t ws_bytes, void* stream);
 
+/* How often the workgroups that add up the chunks of a decode call look for partial results that are not there yet before
+ * they leave them to the last workgroup of the launch (each look takes half a microsecond): 0, never wait; negative, the
+ * default.  The results are the same bit for bit.  Not while calls on the plan are being made. */
+PUREKV_API int purekv_plan_set_decode_polls(purekv_plan_t* plan, int32_t polls);
 
 /*
  * Layer stack (Sec. 3.1 and the layer-index study of the hyperparameter analysis, Sec. 4.5): which layer runs which attention and whose

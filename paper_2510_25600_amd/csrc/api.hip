@@ -280,7 +280,7 @@ int purekv_workspace_init(const purekv_plan_t* p, int op, void* ws, size_t ws_by
   if (ws == nullptr || ws_bytes < need) return PUREKV_EWORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (op == PUREKV_OP_PREFILL) return launch_prefill_ws_init(*p, ws, st);
-  if (op == PUREKV_OP_DECODE) return launch_decode_ws_init(*p, ws, st);
+  if (op == PUREKV_OP_DECODE) return launch_decode_ws_init(ws, ws_bytes, st);
   return PUREKV_OK;   // the other workspaces hold nothing that outlives a call
 }
 
@@ -397,6 +397,12 @@ int purekv_decode_step(const purekv_plan_t* p, const void* q_new, const void* k_
   if (n_cached < 0 || n_cached >= cap) return PUREKV_EINVAL;
   if (ws == nullptr || ws_bytes < decode_ws_bytes(*p, cap)) return PUREKV_EWORKSPACE;
   return launch_decode(*p, q_new, k_new, v_new, kc, vc, n_cached + 1, cap, out, ws, static_cast<hipStream_t>(stream));
+}
+
+int purekv_plan_set_decode_polls(purekv_plan_t* p, int32_t polls) {
+  if (p == nullptr) return PUREKV_EINVAL;
+  p->decode_polls = polls < 0 ? -1 : polls;
+  return PUREKV_OK;
 }
 
 // ---- layer stack: which layer runs which attention, which C drives which layer's selection ----

@@ -517,6 +517,34 @@ def test_decode_step_merges_many_chunks(hq, hkv, d, n0):
     check_attention(f64_of(outs[0]), orc.decode_attention(F64(q), F64(kc_h), F64(vc_h)), f"decode {hq}/{hkv} d={d} n={n0 + 1}")
 
 
+@pytest.mark.parametrize("hq,hkv,d,ns", [
+    (28, 4, 128, (128, 129, 256, 257)),     # one chunk of 128, of 256, the first cut caches
+    (28, 4, 128, (57 * 128, 57 * 128 + 1)),  # 256 compute units hold 57 chunks per KV head beside 28 gathering workgroups
+    (8, 8, 64, (31 * 256, 31 * 256 + 1, 64 * 512 + 1)),   # chunks of 256, then 512; a second pass over 65 chunks
+    (300, 1, 64, (600,)),                   # more heads than compute units: 19 head blocks, the last with 12 heads
+    (5, 5, 128, (300,)),                    # more planes than one for the gathering workgroups would not help: one head each
+])
+def test_decode_gathers_chunks_of_every_size(hq, hkv, d, ns):
+    """Chunks of 128, 256 and 512 keys, added up by the gathering workgroups or, where these never wait, by the last one: the
+    same bits, against the oracle, three calls each on one workspace (which every call leaves at zero)."""
+    from workloads import f32_to_bf16_bits
+    rng = np.random.default_rng(hq + ns[0])
+    cap = max(ns)
+    q, k, v = (f32_to_bf16_bits(rng.standard_normal((x, y, d)).astype(np.float32)) for x, y in ((hq, 1), (hkv, cap), (hkv, cap)))
+    v[:, ::7] = 0    # partial outputs that are exactly zero
+    v[:, :, 5] = 0
+    plan = pk.Plan(1, 4, 4, 4, hq, hkv, d, 3)
+    qd, kd, vd = to_dev(q[:, 0]), to_dev(k), to_dev(v)
+    for n in ns:
+        outs = []
+        for polls in (-1, 0, -1, 0, 1, -1):
+            plan.set_decode_polls(polls)
+            outs.append(bits_of(pk.purekv_decode_attn(plan, qd, kd, vd, n)))
+        assert all(np.array_equal(outs[0], o) for o in outs[1:]), f"{hq}/{hkv} n={n}"
+        check_attention(f64_of(torch.from_numpy(outs[0].view(np.int16)).view(torch.bfloat16)),
+                        orc.decode_attention(F64(q[:, 0]), F64(k[:, :n]), F64(v[:, :n])), f"decode {hq}/{hkv} d={d} n={n}")
+
+
 @pytest.mark.parametrize("hq,hkv,d,n0", [(2, 1, 64, 64 * 256 + 40), (2, 1, 128, 128 * 256 + 40), (2, 1, 64, 700)])
 def test_decode_step_with_scores_of_minus_infinity(hq, hkv, d, n0):
     """Keys whose scores overflow to -inf have no weight, also where they fill every chunk of the final merge's first pass
