@@ -156,16 +156,19 @@ static int create_on_device(const purekv_shape_t* shape, const uint8_t* head_mas
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const size_t sb = p->stream.size() * sizeof(StreamEntry), ub = p->units.size() * sizeof(Unit),
-               qb = p->queue_begin.size() * sizeof(int32_t);
+               qb = (size_t)p->n_queues * sizeof(QueueHead);
+  std::vector<QueueHead> heads((size_t)p->n_queues);
+  for (int32_t q = 0; q < p->n_queues; ++q) {
+    const int32_t u0 = p->queue_units_begin[q];
+    const Unit& un = p->units[u0];   // (of an empty queue: some other unit's, not looked at)
+    heads[q] = {p->queue_begin[q], p->queue_begin[q + 1], u0, p->queue_units_begin[q + 1], un.row0, un.head0, un.n_splits, un.ws_row0};
+  }
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&p->d_stream), sb ? sb : 16);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_units), ub ? ub : 16);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_queue_begin), qb ? qb : 16);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_queue_unit0), qb ? qb : 16);
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&p->d_queues), qb ? qb : 16);
   if (e == hipSuccess && sb) e = hipMemcpyAsync(p->d_stream, p->stream.data(), sb, hipMemcpyHostToDevice, st);
   if (e == hipSuccess && ub) e = hipMemcpyAsync(p->d_units, p->units.data(), ub, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && qb) e = hipMemcpyAsync(p->d_queue_begin, p->queue_begin.data(), qb, hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && qb)
-    e = hipMemcpyAsync(p->d_queue_unit0, p->queue_units_begin.data(), qb, hipMemcpyHostToDevice, st);
+  if (e == hipSuccess && qb) e = hipMemcpyAsync(p->d_queues, heads.data(), qb, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);  // the host vectors must outlive the copies: finish them now
   if (e != hipSuccess) {
     purekv_plan_destroy(p);
@@ -179,8 +182,7 @@ int purekv_plan_destroy(purekv_plan_t* p) {
   if (p == nullptr) return PUREKV_OK;
   if (p->d_stream) (void)hipFree(p->d_stream);
   if (p->d_units) (void)hipFree(p->d_units);
-  if (p->d_queue_begin) (void)hipFree(p->d_queue_begin);
-  if (p->d_queue_unit0) (void)hipFree(p->d_queue_unit0);
+  if (p->d_queues) (void)hipFree(p->d_queues);
   delete p;
   return PUREKV_OK;
 }

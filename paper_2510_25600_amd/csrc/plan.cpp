@@ -545,6 +545,12 @@ void build_plan(purekv_plan& p, int n_cu) {
       if (u + 2 < queues[q].size())   // another unit follows
         p.stream[p.stream.size() - (w.n_tiles >= 2 ? 2 : 1)].need |= kStepFetchQ;
     }
+    const size_t n_units_q = queues[q].size() / 2;
+    for (size_t u = n_units_q, next = 0; u-- > 0;) {   // how far the next slice of the queue, or its end, is
+      Unit& un = p.units[p.units.size() - n_units_q + u];
+      un.to_next_slice = static_cast<int32_t>(++next);
+      if (un.n_splits > 1) next = 0;
+    }
     p.queue_begin.push_back(static_cast<int32_t>(p.stream.size()));
     p.queue_units_begin.push_back(static_cast<int32_t>(p.queue_units.size() / 2));
   }

@@ -75,7 +75,15 @@ struct Unit {
   // s * n_groups * PUREKV_WAVES * 32 rows further -- and the arrival counter of that (query tile, head group)
   int32_t ws_row_first;
   int32_t counter;
-  int32_t pad[2];
+  int32_t to_next_slice;   // units from this one to its queue's next slice of a cut list, or to the queue's end
+  int32_t pad;
+};
+
+// Where a persistent workgroup starts: its queue and the first fields of its first unit, read in one go.
+struct QueueHead {
+  int32_t begin, end;            // of its entries in the stream
+  int32_t unit0, unit_end;       // of its units (units are numbered in stream order)
+  int32_t row0, head0, n_splits, ws_row0;
 };
 
 struct Geometry {
@@ -117,8 +125,7 @@ struct purekv_plan {
   // device copies (null for host-only plans)
   purekv::StreamEntry* d_stream = nullptr;
   purekv::Unit* d_units = nullptr;
-  int32_t* d_queue_begin = nullptr;
-  int32_t* d_queue_unit0 = nullptr;        // [n_queues + 1] first unit of each queue
+  purekv::QueueHead* d_queues = nullptr;
   float* d_static_scores = nullptr;        // the library's static score buffer on this plan's device (not owned)
   // Head subset (empty: every query head).  A plan over a subset lists units for the selected heads only and leaves
   // the other heads' rows of every output untouched; it keeps the stacked workgroup shape when the subset consists
