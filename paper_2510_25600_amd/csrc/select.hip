@@ -7,7 +7,8 @@
 //   select kernel: one workgroup per (layer, KV head).  The h-th largest value is found exactly on the
 //                  order-preserving integer image of the fp32 scores by an MSB-first radix select (rows of up to
 //                  32768 scores stay in registers and are read from memory once; longer rows re-read L2 in
-//                  every pass); an ordered pass then emits, ascending, every
+//                  every pass; where a head's V rows are 128 KB or less, the kernel forms the scores itself: one
+//                  launch); an ordered pass then emits, ascending, every
 //                  index above it plus the lowest-index ties.  Integer work only: the result is the one a
 //                  stable full sort would give.
 #include <mutex>
@@ -22,7 +23,33 @@ constexpr int SEL_THREADS = 1024;
 // Order-preserving map from fp32 to uint32 (-0.0 first folded onto +0.0).
 __device__ __forceinline__ uint32_t sort_key(float s) {
   const uint32_t u = __float_as_uint(s + 0.0f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
+// One lane's share (16 bytes) of a V row's sum of squares, and the sum over the row's LPR lanes, in each of them, on the DPP path
+// (lane ^ 1, lane ^ 2, then mirrors of 8 and 16, where all lanes of a quad or half row already agree: the partners, and with
+// them the sums bit for bit, of a butterfly of shuffles, which goes through the LDS crossbar).
+__device__ __forceinline__ float piece_norm2(u32x4 x) {
+  float ss = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float lo = bf16_lo(x[w]), hi = bf16_hi(x[w]);
+    ss += lo * lo + hi * hi;
+  }
+  return ss;
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_partner(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, false));
+}
+template <int LPR>
+__device__ __forceinline__ float row_norm2(float ss) {
+  static_assert(LPR == 8 || LPR == 16);
+  ss += dpp_partner<0xB1>(ss);
+  ss += dpp_partner<0x4E>(ss);
+  ss += dpp_partner<0x141>(ss);
+  if (LPR == 16) ss += dpp_partner<0x140>(ss);
+  return ss;
 }
 
 // grid = (row blocks, layers * Hkv): a workgroup streams SCORE_ROWS consecutive rows of one (layer, KV head).
@@ -45,24 +72,28 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
   v += dpp_move<0x143, 0xc>(0u, v);
   return v;
 }
-// Minimum / maximum over the wavefront, valid in lane 63 (the scans run upwards).
-__device__ __forceinline__ uint32_t wave_scan_min(uint32_t v) {
+// Minimum / maximum over the wavefront, valid in lane 63 (the scans run upwards); over each row of 16 lanes, in its last one.
+__device__ __forceinline__ uint32_t row_scan_min(uint32_t v) {
   v = min(v, dpp_move<0x111, 0xf>(0xffffffffu, v));
   v = min(v, dpp_move<0x112, 0xf>(0xffffffffu, v));
   v = min(v, dpp_move<0x114, 0xf>(0xffffffffu, v));
-  v = min(v, dpp_move<0x118, 0xf>(0xffffffffu, v));
-  v = min(v, dpp_move<0x142, 0xa>(0xffffffffu, v));
-  v = min(v, dpp_move<0x143, 0xc>(0xffffffffu, v));
-  return v;
+  return min(v, dpp_move<0x118, 0xf>(0xffffffffu, v));
 }
-__device__ __forceinline__ uint32_t wave_scan_max(uint32_t v) {
+__device__ __forceinline__ uint32_t row_scan_max(uint32_t v) {
   v = max(v, dpp_move<0x111, 0xf>(0u, v));
   v = max(v, dpp_move<0x112, 0xf>(0u, v));
   v = max(v, dpp_move<0x114, 0xf>(0u, v));
-  v = max(v, dpp_move<0x118, 0xf>(0u, v));
+  return max(v, dpp_move<0x118, 0xf>(0u, v));
+}
+__device__ __forceinline__ uint32_t wave_scan_min(uint32_t v) {
+  v = row_scan_min(v);
+  v = min(v, dpp_move<0x142, 0xa>(0xffffffffu, v));
+  return min(v, dpp_move<0x143, 0xc>(0xffffffffu, v));
+}
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t v) {
+  v = row_scan_max(v);
   v = max(v, dpp_move<0x142, 0xa>(0u, v));
-  v = max(v, dpp_move<0x143, 0xc>(0u, v));
-  return v;
+  return max(v, dpp_move<0x143, 0xc>(0u, v));
 }
 
 template <int D>
@@ -84,14 +115,7 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ c,
   }
 #pragma unroll
   for (int u = 0; u < SCORE_UNROLL; ++u) {
-    float ss = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float lo = bf16_lo(x[u][w]), hi = bf16_hi(x[u][w]);
-      ss += lo * lo + hi * hi;
-    }
-#pragma unroll
-    for (int o = 1; o < LPR; o <<= 1) ss += __shfl_xor(ss, o, 64);
+    const float ss = row_norm2<LPR>(piece_norm2(x[u]));
     const int j = j0 + u * RPB;
     if (sub == 0 && j < n_keys) s_out[(int64_t)lk * n_keys + j] = c[(int64_t)kvh * n_keys + j] * __builtin_sqrtf(ss);
   }
@@ -115,14 +139,7 @@ __global__ __launch_bounds__(256) void vnorm2_kernel(const uint16_t* __restrict_
   }
 #pragma unroll
   for (int u = 0; u < SCORE_UNROLL; ++u) {
-    float ss = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float lo = bf16_lo(x[u][w]), hi = bf16_hi(x[u][w]);
-      ss += lo * lo + hi * hi;
-    }
-#pragma unroll
-    for (int o = 1; o < LPR; o <<= 1) ss += __shfl_xor(ss, o, 64);
+    const float ss = row_norm2<LPR>(piece_norm2(x[u]));
     const int j = j0 + u * RPB;
     if (sub == 0 && j < N) n2_out[(int64_t)kvh * N + j] = ss;
   }
@@ -165,53 +182,104 @@ __device__ __forceinline__ void block_scan2(uint32_t& a, uint32_t& b, uint32_t* 
 // EPT = scores per thread: element e of thread t is score e * 1024 + t, so loads are whole cache lines, the scores are read
 // from memory once (their integer images stay in registers) and a wavefront's elements of one e are 64 consecutive indices.
 //
-// MSB-first radix select, 8 bits a pass, LDS histogram.  The passes start at the highest bit in which the keys
-// differ at all (floats of similar size share sign and most of the exponent: starting at bit 31 would send every
-// key to one or two bins, and LDS atomics to one address are serialised); below that bit the digits spread, and two passes
-// usually leave a handful of candidates for the h-th largest key: SEL_LIST or fewer are ranked directly.
+// MSB-first radix select on the keys' distances from the smallest one, 12 bits a pass, LDS histogram of 4096 bins: a row's range
+// is some 14 octaves, so a bin of the first pass holds a 64th of an octave or so and the h-th largest key shares it with a
+// few dozen others.  SEL_LIST or fewer are ranked directly, one candidate a wavefront at a time.
 //
-// A row is one workgroup's chain of barriers and LDS round trips; what counts is how many.  A pass has two (the histogram
-// has two buffers, the idle one is cleared behind the scan), the ranks of the kept keys one: ballots count the kept keys of
-// every 64 consecutive indices, and each wavefront scans the table of those counts by itself.
-// (A contiguous chunk of scores per thread staged through LDS, three barriers a pass and passes down to the last bit took 9.0
-// us for 8192 log-normal scores x 4 KV heads and 14.7 for 16384 x 4, this 7.3 and 11.3: kernel trace, calls of this kernel
-// one after the other, median of 120.  Between the other kernels of a layer 8192 x 4 took 9.4 and take 8.9.  The 16
-// wavefronts' vector instructions on one CU are about half of it.)
-constexpr uint32_t SEL_LIST = 32;
-template <int EPT>
-__global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __restrict__ s, int32_t* __restrict__ idx_out,
-                                                             int32_t N, int32_t w, int32_t h) {
-  constexpr int WAVES = SEL_THREADS / 64, HCOPIES = 16, HSTRIDE = 260, HWORDS = HCOPIES * HSTRIDE;
-  constexpr int TPL = EPT * WAVES / 64;   // entries of the table of counts per lane
+// A row is one workgroup's chain of barriers and LDS round trips and its 16 wavefronts' vector instructions on one CU; what
+// counts is how few of both there are.  The histogram has two buffers, the idle one is cleared behind the scan; ballots count
+// the kept keys of every 64 consecutive indices, and each wavefront scans the table of those counts by itself; a row without a
+// tie at the threshold needs one comparison a key for that, not two.  Log-normal scores x 4 KV heads between the other
+// kernels of a layer (kernel trace, median): 4199 6.9 -> 5.0 us, 8192 7.2 -> 6.2, 16384 10.9 -> 8.7; 8192 x 104 8.0 -> 6.4.  (Before:
+// digits of 8 bits of the keys as they are, which for scores about a power of 16 hold the exponent and little else, so two passes;
+// all wavefronts ranked all candidates.  Histogram in two copies of 2048 bins: 16384 9.3.  Lists of 128: no change.)
+constexpr uint32_t SEL_LIST = 64;
+// A layer's V of up to 128 KB per KV head (eight loads of 16 bytes per thread, all in flight together) is read by the selecting
+// workgroup itself: one round trip to memory instead of a launch, its drain and the scores' way through memory.  256 keys of 64:
+// 3.8 + 5.1 us in two launches, 4.0 in one.  Beyond that a single CU pulls the rows in slower than the chip does.
+constexpr int kFusedBytes = 128 * 1024;
+struct ScoreArgs {   // what the scores are formed from: arguments of purekv_topk_select
+  const float* c;
+  const uint16_t* v;
+  int64_t v_layer_stride, v_head_stride, v_tok_stride;
+  float* s_out;      // or null
+  int32_t Hkv;
+};
+// D != 0: the scores are not read but formed here, from C and V (rows of D elements; at most kFusedBytes of them).
+template <int EPT, int D>
+__global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __restrict__ s, const ScoreArgs sa,
+                                                             int32_t* __restrict__ idx_out, int32_t N, int32_t w, int32_t h) {
+  // Histogram: 4096 bins.  Bin b sits at word b + 4 (b / 64): the scan's lanes, 64 bins each, then read 16 bytes a lane from
+  // different banks.
+  constexpr int WAVES = SEL_THREADS / 64, HBITS = 12, HWORDS = 4096 + 4 * 64;
+  constexpr int TPL = (EPT * WAVES + 63) / 64;   // entries of the table of counts per lane
+  static_assert(WAVES % TPL == 0, "entry e * WAVES + w is entry w % TPL of its lane");
   __shared__ __attribute__((aligned(16))) uint32_t hist[2][HWORDS];
-  __shared__ __attribute__((aligned(16))) uint32_t counts[EPT * WAVES];   // [e][wavefront] kept keys: above | equal << 16
+  __shared__ __attribute__((aligned(16))) uint32_t counts[64 * TPL];   // [e][wavefront] kept keys: above | equal << 16
   __shared__ uint32_t ext[2][WAVES];      // per-wavefront minimum and maximum key
   __shared__ uint32_t list[SEL_LIST];
   __shared__ uint32_t list_n;
   __shared__ uint32_t sel[3];             // chosen digit, remaining count, keys with that digit
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_keys = N - w;
-  const float* sv = s + (size_t)blockIdx.x * n_keys;
   int32_t* out = idx_out + (size_t)blockIdx.x * (h + w);
 
-  if (h == 0) {
+  if (h == 0 && (D == 0 || sa.s_out == nullptr)) {
     for (int t = tid; t < w; t += SEL_THREADS) out[t] = N - w + t;
     return;
   }
   float raw[EPT];
+  auto clear = [&]() {
+    for (int t = tid; t < w; t += SEL_THREADS) out[h + t] = N - w + t;
+    for (int i = tid; i < HWORDS; i += SEL_THREADS) hist[0][i] = 0;
+    if (tid == 0) list_n = 0;
+  };
+  if constexpr (D == 0) {
+    const float* sv = s + (size_t)blockIdx.x * n_keys;
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) raw[e] = sv[min(e * SEL_THREADS + tid, n_keys - 1)];
-  for (int t = tid; t < w; t += SEL_THREADS) out[h + t] = N - w + t;
-  for (int i = tid; i < HWORDS; i += SEL_THREADS) hist[0][i] = 0;
-  if (tid == 0) list_n = 0;
-  // Elements past the end of the row become key 0, below every score's key: they are never among the h <= n_keys largest,
-  // so nothing behind this loop asks which elements exist.
+    for (int e = 0; e < EPT; ++e) raw[e] = sv[min(e * SEL_THREADS + tid, n_keys - 1)];
+    clear();
+  } else {
+    constexpr int LPR = D / 8, RPB = SEL_THREADS / LPR, UNROLL = kFusedBytes / (SEL_THREADS * 16);
+    static_assert(UNROLL * RPB <= EPT * SEL_THREADS && UNROLL * RPB <= HWORDS, "rows, and their scores in the idle histogram");
+    float* const sc = reinterpret_cast<float*>(hist[1]);
+    const int layer = blockIdx.x / sa.Hkv, kvh = blockIdx.x - layer * sa.Hkv, sub = tid % LPR, row = tid / LPR;
+    const uint16_t* vh = sa.v + (int64_t)layer * sa.v_layer_stride + (int64_t)kvh * sa.v_head_stride + sub * 8;
+    u32x4 x[UNROLL];
+    float cj[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      if (u * RPB >= n_keys) break;
+      const int j = min(u * RPB + row, n_keys - 1);
+      x[u] = *reinterpret_cast<const u32x4*>(vh + (int64_t)j * sa.v_tok_stride);
+      cj[u] = sa.c[(int64_t)kvh * n_keys + j];
+    }
+    clear();
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      if (u * RPB >= n_keys) break;
+      const float score = cj[u] * __builtin_sqrtf(row_norm2<LPR>(piece_norm2(x[u])));
+      const int j = u * RPB + row;
+      if (sub == 0 && j < n_keys) {
+        sc[j] = score;
+        if (sa.s_out != nullptr) sa.s_out[(int64_t)blockIdx.x * n_keys + j] = score;
+      }
+    }
+    if (h == 0) return;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) raw[e] = sc[min(e * SEL_THREADS + tid, n_keys - 1)];
+  }
+  // Keys are the scores' images less the smallest one, plus 1: the highest digit then tells apart what the row's range holds (of
+  // keys as they are it tells apart exponents and little else when these lie about a power of 16).  Elements past the end of
+  // the row (they were loaded as its last one) become key 0, below every score's: they are never among the h <= n_keys
+  // largest.
   uint32_t key[EPT];
-  uint32_t kmin = 0xffffffffu, kmax = 0u;   // kmin: of key - 1 (key 0 wraps to the top)
+  uint32_t kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
-    key[e] = e * SEL_THREADS + tid < n_keys ? max(sort_key(raw[e]), 1u) : 0u;
-    kmin = min(kmin, key[e] - 1u);
+    key[e] = max(sort_key(raw[e]), 1u);
+    kmin = min(kmin, key[e]);
     kmax = max(kmax, key[e]);
   }
   kmin = wave_scan_min(kmin);
@@ -221,57 +289,60 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
     ext[1][wave] = kmax;
   }
   __syncthreads();
-  {  // lanes 0..15 hold the wavefronts' minima, lanes 16..31 their maxima: one row of 16 lanes each
-    const uint32_t e0 = lane < 16 ? ext[0][lane] : 0xffffffffu, e1 = (lane >= 16 && lane < 32) ? ext[1][lane - 16] : 0u;
-    uint32_t mn = e0, mx = e1;
-    mn = min(mn, dpp_move<0x111, 0xf>(0xffffffffu, mn));
-    mn = min(mn, dpp_move<0x112, 0xf>(0xffffffffu, mn));
-    mn = min(mn, dpp_move<0x114, 0xf>(0xffffffffu, mn));
-    mn = min(mn, dpp_move<0x118, 0xf>(0xffffffffu, mn));
-    mx = max(mx, dpp_move<0x111, 0xf>(0u, mx));
-    mx = max(mx, dpp_move<0x112, 0xf>(0u, mx));
-    mx = max(mx, dpp_move<0x114, 0xf>(0u, mx));
-    mx = max(mx, dpp_move<0x118, 0xf>(0u, mx));
-    kmin = __builtin_amdgcn_readlane(mn, 15) + 1u;
-    kmax = __builtin_amdgcn_readlane(mx, 31);
+  static_assert(WAVES == 16, "a row of 16 lanes holds the wavefronts'");
+  kmin = __builtin_amdgcn_readlane(row_scan_min(ext[0][lane & 15]), 15);
+  kmax = __builtin_amdgcn_readlane(row_scan_max(ext[1][lane & 15]), 15);
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    key[e] -= kmin - 1u;
+    if ((e + 1) * SEL_THREADS > n_keys) key[e] = e * SEL_THREADS + tid < n_keys ? key[e] : 0u;
   }
-  // bits above `top` are common to all keys
-  int top = 31 - __clz((int)(kmin ^ kmax));   // -1 when all keys are equal
-  uint32_t prefix = top >= 31 ? 0u : (top < 0 ? kmax : (kmax >> (top + 1)) << (top + 1));
+  // highest bit of a key; -1 when all are equal (to 1)
+  int top = kmax != kmin ? 31 - __clz((int)(kmax - kmin + 1u)) : -1;
+  uint32_t prefix = top < 0 ? 1u : 0u;
+  bool first_pass = true, all_ties = false;   // all_ties: every key equal to the h-th largest is kept
   uint32_t remaining = (uint32_t)h;
   int buf = 0;
+  auto word_of = [](uint32_t bin) { return bin + 4u * (bin >> 6); };
   while (top >= 0) {
-    const int shift = max(top - 7, 0);
+    const int shift = max(top - (HBITS - 1), 0);
     const uint32_t dmask = (2u << (top - shift)) - 1u;           // digit = bits top .. shift
-    const uint32_t cmask = top >= 31 ? 0u : ~((2u << top) - 1u); // bits above the digit decide candidacy
-    // LDS atomics to one address are serialised, and digits made of exponent bits are shared by many lanes: lane
-    // l counts in copy l % 16 of the histogram (copies 260 words apart, so one bin's copies sit in 16 banks).
-    uint32_t* const my_hist = hist[buf] + (lane & (HCOPIES - 1)) * HSTRIDE;
+    // candidates behind the first pass: keys of [prefix, prefix + 2^(top + 1)), but not 0
+    const uint32_t lo = max(prefix, 1u), width = (2u << top) - (lo - prefix);
+    uint32_t* const my_hist = hist[buf];
+    if (first_pass) {   // every score is a candidate
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const uint32_t u = key[e];
-      if ((u & cmask) == prefix) atomicAdd(&my_hist[(u >> shift) & dmask], 1u);
+      for (int e = 0; e < EPT; ++e) {
+        const uint32_t u = key[e];
+        if ((e + 1) * SEL_THREADS <= n_keys || u != 0u) atomicAdd(&my_hist[word_of((u >> shift) & dmask)], 1u);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const uint32_t u = key[e];
+        if (u - lo < width) atomicAdd(&my_hist[word_of((u >> shift) & dmask)], 1u);
+      }
     }
+    first_pass = false;
     __syncthreads();
     if (wave == 0) {
-      // lane t owns digits 255-4t .. 252-4t (descending); find where the count from the top reaches `remaining`
+      // lane t owns digits 4095 - 64 t .. 4032 - 64 t; find where the count from the top reaches `remaining`: first the lane,
+      // then, its 64 bins over the lanes, the digit
+      const uint32_t* const mine_h = hist[buf] + 68 * (63 - lane);
       u32x4 c4 = {0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int cp = 0; cp < HCOPIES; ++cp) c4 += *reinterpret_cast<const u32x4*>(hist[buf] + cp * HSTRIDE + 252 - 4 * lane);
+      for (int i = 0; i < 16; ++i) c4 += *reinterpret_cast<const u32x4*>(mine_h + 4 * i);
       const uint32_t tot = (c4[0] + c4[1]) + (c4[2] + c4[3]);
       const uint32_t inc = wave_scan_add(tot);
-      const uint32_t before = inc - tot;  // elements with larger digits than this lane's
-      if (before < remaining && remaining <= inc) {
-        uint32_t run = before;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          if (run < remaining && remaining <= run + c4[3 - r]) {
-            sel[0] = 255 - 4 * lane - r;
-            sel[1] = remaining - run;
-            sel[2] = c4[3 - r];
-          }
-          run += c4[3 - r];
-        }
+      const int at = __ffsll((unsigned long long)__ballot(inc >= remaining)) - 1;   // (the last lane's is at least `remaining`)
+      const uint32_t before = __builtin_amdgcn_readlane(inc, at) - __builtin_amdgcn_readlane(tot, at);
+      const uint32_t count = hist[buf][68 * (63 - at) + (63 - lane)];
+      const uint32_t upto = before + wave_scan_add(count);
+      const int in = __ffsll((unsigned long long)__ballot(upto >= remaining)) - 1;
+      if (lane == in) {
+        sel[0] = 4095 - 64 * at - in;
+        sel[1] = remaining - (upto - count);
+        sel[2] = count;
       }
     } else {
       for (int i = tid - 64; i < HWORDS; i += SEL_THREADS - 64) hist[buf ^ 1][i] = 0;
@@ -282,37 +353,50 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
     const uint32_t n_cand = sel[2];
     buf ^= 1;
     top = shift - 1;
+    all_ties = remaining == n_cand;   // (read behind the last pass)
     if (top >= 0 && n_cand <= SEL_LIST) {
-      // few keys share the prefix: gather them (in any order) and rank them; every wavefront for itself
-      const uint32_t lmask = ~((2u << top) - 1u);
+      // few keys share the prefix: gather them (in any order) and rank them, a candidate a wavefront at a time
+      const uint32_t from = max(prefix, 1u), n_keys_of = (2u << top) - (from - prefix);
 #pragma unroll
       for (int e = 0; e < EPT; ++e)
-        if ((key[e] & lmask) == prefix) list[atomicAdd(&list_n, 1u)] = key[e];   // n_cand of them
+        if (key[e] - from < n_keys_of) list[atomicAdd(&list_n, 1u)] = key[e];   // n_cand of them
       __syncthreads();
-      const uint32_t mine = lane < (int)n_cand ? list[lane] : 0u;
-      uint32_t above = 0, from = 0;   // listed keys greater than / not less than this lane's
-      for (uint32_t i = 0; i < n_cand; ++i) {
-        const uint32_t k = __builtin_amdgcn_readlane(mine, i);
-        above += k > mine;
-        from += k >= mine;
+      const uint32_t other = lane < (int)n_cand ? list[lane] : 0u;   // (below every candidate)
+      for (int i = wave; i < (int)n_cand; i += WAVES) {
+        const uint32_t cand = __builtin_amdgcn_readlane(other, i);
+        const uint32_t above = (uint32_t)__popcll(__ballot(other > cand)), upto = (uint32_t)__popcll(__ballot(other >= cand));
+        if (above < remaining && remaining <= upto && lane == 0) {   // (equal candidates write the same)
+          sel[0] = cand;
+          sel[1] = remaining - above;
+          sel[2] = upto - above;
+        }
       }
-      const uint64_t hit = __ballot(lane < (int)n_cand && above < remaining && remaining <= from);
-      const int at = hit != 0 ? __ffsll((unsigned long long)hit) - 1 : 0;
-      prefix = __builtin_amdgcn_readlane(mine, at);
-      remaining -= __builtin_amdgcn_readlane(above, at);
+      __syncthreads();
+      prefix = sel[0];
+      remaining = sel[1];
+      all_ties = remaining == sel[2];
       break;
     }
   }
   // prefix = key of the h-th largest score; `remaining` of the keys equal to it are kept (lowest indices)
   const uint32_t tau = prefix, need = remaining;
+  // With no tie to break (nearly always), a kept key is one that is not less than tau: one comparison, one rank.
   uint32_t mine = 0;   // lane e: counts of this wavefront's element e
+  if (all_ties) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const uint32_t gt = (uint32_t)__popcll(__ballot(key[e] > tau));
-    const uint32_t eq = (uint32_t)__popcll(__ballot(key[e] == tau));
-    mine = lane == e ? (gt | eq << 16) : mine;   // sums stay below 2^16 (above, at most h - 1) and within 2^16 (equal)
+    for (int e = 0; e < EPT; ++e) {
+      const uint32_t ge = (uint32_t)__popcll(__ballot(key[e] >= tau));
+      mine = lane == e ? ge : mine;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {   // sums stay below 2^16 (above, at most h - 1) and within 2^16 (equal)
+      const uint32_t gt = (uint32_t)__popcll(__ballot(key[e] > tau)), eq = (uint32_t)__popcll(__ballot(key[e] == tau));
+      mine = lane == e ? (gt | eq << 16) : mine;
+    }
   }
   if (lane < EPT) counts[lane * WAVES + wave] = mine;
+  if (EPT * WAVES % 64 != 0 && tid >= EPT * WAVES && tid < 64 * TPL) counts[tid] = 0;
   __syncthreads();
   // exclusive scan of the table (in order of the index), TPL entries per lane; of those, entry wave % TPL is the one this
   // wavefront asks some lane for
@@ -325,15 +409,27 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
   uint32_t base = wave_scan_add(tot) - tot;
 #pragma unroll
   for (int i = 0; i < TPL - 1; ++i) base += i < wave % TPL ? ent[i] : 0u;
+  auto rank = [](uint64_t m, uint32_t before) {   // of the lane among those of m
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
+  };
+  if (all_ties) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    if (e * SEL_THREADS >= n_keys) break;
-    const uint32_t b = __builtin_amdgcn_readlane(base, (e * WAVES + wave) / TPL);
-    const bool is_gt = key[e] > tau, is_eq = key[e] == tau;
-    const uint64_t mg = __ballot(is_gt), me = __ballot(is_eq);
-    const uint32_t gt = (b & 0xffffu) + __builtin_amdgcn_mbcnt_hi((uint32_t)(mg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mg, 0u));
-    const uint32_t eq = (b >> 16) + __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0u));
-    if (is_gt || (is_eq && eq < need)) out[gt + min(eq, need)] = e * SEL_THREADS + tid;
+    for (int e = 0; e < EPT; ++e) {
+      if (e * SEL_THREADS >= n_keys) break;
+      const uint32_t b = __builtin_amdgcn_readlane(base, (e * WAVES + wave) / TPL);
+      const bool kept = key[e] >= tau;
+      const uint32_t at = rank(__ballot(kept), b);
+      if (kept) out[at] = e * SEL_THREADS + tid;
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      if (e * SEL_THREADS >= n_keys) break;
+      const uint32_t b = __builtin_amdgcn_readlane(base, (e * WAVES + wave) / TPL);
+      const bool is_gt = key[e] > tau, is_eq = key[e] == tau;
+      const uint32_t gt = rank(__ballot(is_gt), b & 0xffffu), eq = rank(__ballot(is_eq), b >> 16);
+      if (is_gt || (is_eq && eq < need)) out[gt + min(eq, need)] = e * SEL_THREADS + tid;
+    }
   }
 }
 
@@ -515,6 +611,17 @@ int launch_topk(const purekv_plan& p, const float* c, const void* v, int64_t v_l
                 int32_t w, int32_t h, int32_t* idx_out, float* s_out, void* ws, hipStream_t st) {
   const int32_t n_keys = p.g.N - w;
   const float* scores = c;
+  if (v != nullptr && n_keys > 0 && (int64_t)n_keys * p.g.d * 2 <= kFusedBytes) {
+    const ScoreArgs sa{c, static_cast<const uint16_t*>(v), v_layer_stride, p.g.kv_sh, p.g.kv_st, s_out, p.g.Hkv};
+    const dim3 grid((unsigned)(n_layers * p.g.Hkv));
+    const float* none = nullptr;
+    if (p.g.d == 128)
+      hipLaunchKernelGGL((select_kernel<1, 128>), grid, dim3(SEL_THREADS), 0, st, none, sa, idx_out, p.g.N, w, h);
+    else
+      hipLaunchKernelGGL((select_kernel<1, 64>), grid, dim3(SEL_THREADS), 0, st, none, sa, idx_out, p.g.N, w, h);
+    PUREKV_HIP_TRY(hipGetLastError());
+    return PUREKV_OK;
+  }
   if (v != nullptr && n_keys > 0) {
     float* sbuf = s_out ? s_out : static_cast<float*>(ws);
     const int rows_per_block = (256 / (p.g.d / 8)) * SCORE_UNROLL;
@@ -537,15 +644,23 @@ static int launch_select(const purekv_plan& p, const float* scores, int32_t n_la
   const int32_t n_keys = p.g.N - w;
   const dim3 sgrid((unsigned)(n_layers * p.g.Hkv)), sblock(SEL_THREADS);
   const int per_thread = (n_keys + SEL_THREADS - 1) / SEL_THREADS;
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, sgrid, sblock, 0, st, scores, idx_out, p.g.N, w, h); };
-  if (per_thread <= 8)
-    launch(select_kernel<8>);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, sgrid, sblock, 0, st, scores, ScoreArgs{}, idx_out, p.g.N, w, h); };
+  if (per_thread <= 1)
+    launch(select_kernel<1, 0>);
+  else if (per_thread <= 2)
+    launch(select_kernel<2, 0>);
+  else if (per_thread <= 4)
+    launch(select_kernel<4, 0>);
+  else if (per_thread <= 6)
+    launch(select_kernel<6, 0>);
+  else if (per_thread <= 8)
+    launch(select_kernel<8, 0>);
   else if (per_thread <= 16)
-    launch(select_kernel<16>);
+    launch(select_kernel<16, 0>);
   else if (per_thread <= 32)
-    launch(select_kernel<32>);
+    launch(select_kernel<32, 0>);
   else
-    launch(select_kernel_stream);
+    hipLaunchKernelGGL(select_kernel_stream, sgrid, sblock, 0, st, scores, idx_out, p.g.N, w, h);
   PUREKV_HIP_TRY(hipGetLastError());
   return PUREKV_OK;
 }

@@ -397,6 +397,52 @@ def test_topk_negative_and_mixed_scores():
         assert np.array_equal(idx.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("d,n_keys", [(64, 1), (64, 127), (64, 1023), (64, 1024), (64, 1025), (128, 63), (128, 511), (128, 512), (128, 513)])
+@pytest.mark.parametrize("layers", [1, 3])
+def test_selection_that_forms_its_scores(d, n_keys, layers):
+    """Up to 128 KB of V rows per KV head the selecting workgroup forms the scores itself: bit for bit those of the score
+    kernel (the same rows at the head of a longer layer), and the choice that follows from them."""
+    w, longer, hkv = 9, 1200, 3
+    rng = np.random.default_rng(n_keys + d + layers)
+    v = torch.from_numpy(rng.standard_normal((layers, hkv, n_keys + longer + w, d)).astype(np.float32)).bfloat16().cuda()
+    c = torch.from_numpy(np.exp(rng.standard_normal((hkv, n_keys + longer))).astype(np.float32)).cuda()
+    small, large = pk.Plan(1, 1, n_keys, w, hkv, hkv, d, 0), pk.Plan(1, 1, n_keys + longer, w, hkv, hkv, d, 0)
+    _, s_ref = pk.purekv_topk_select(large, c, v, w, 1, want_scores=True)
+    s_ref = s_ref.reshape(layers, hkv, -1)[:, :, :n_keys]
+    vs, cs = v[:, :, :n_keys + w].contiguous(), c[:, :n_keys].contiguous()
+    for h in sorted({0, 1, n_keys // 3, n_keys}):
+        idx, s = pk.purekv_topk_select(small, cs, vs, w, h, want_scores=True)
+        again = pk.purekv_topk_select(small, cs, vs, w, h)
+        assert torch.equal(s.reshape(s_ref.shape).view(torch.int32), s_ref.contiguous().view(torch.int32))
+        assert torch.equal(idx, again)
+        for l in range(layers):
+            ref = orc.topk_select(s_ref[l].cpu().numpy().astype(np.float64), h, n_keys + w, w)
+            assert np.array_equal(idx.reshape(layers, hkv, -1)[l].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n_keys", [65, 1024, 1025, 2049, 4097, 6144, 6145, 16385])
+def test_topk_exact_on_scores_of_any_range(n_keys):
+    """Rows over the whole range of fp32 (infinities and the smallest and largest numbers of both signs), within a few units in
+    the last place (also but for one key), of one value (likewise), and of two values that share the threshold among them."""
+    w, rng = 5, np.random.default_rng(n_keys)
+    bits = rng.integers(0, 2 ** 32, n_keys, dtype=np.uint64).astype(np.uint32)
+    wide = bits.view(np.float32).copy()
+    wide[~np.isfinite(wide)] = np.inf
+    wide[:7] = [np.inf, -np.inf, 3.4028235e38, -3.4028235e38, 1e-45, -1e-45, -0.0]
+    near = (np.float32(1.5).view(np.uint32) + rng.integers(0, 40, n_keys).astype(np.uint32)).view(np.float32)
+    one = np.full(n_keys, -2.5, np.float32)
+    two = np.where(rng.random(n_keys) < 0.5, np.float32(0.25), np.float32(0.75)).astype(np.float32)
+    but_one = one.copy()
+    but_one[n_keys // 2] = 1e30
+    near_but_one = near.copy()   # all but one key in one bin of the first pass
+    near_but_one[n_keys // 3] = 1e30
+    s = np.stack([wide, near, one, two, but_one, near_but_one])
+    plan = pk.Plan(1, 1, n_keys, w, 6, 6, 64, 0)
+    for h in (1, 2, 65, n_keys // 5 + 1, n_keys // 2, n_keys - 1, n_keys):
+        idx = pk.purekv_topk_select(plan, torch.from_numpy(s).cuda(), None, w, min(h, n_keys))
+        assert np.array_equal(idx.cpu().numpy(), orc.topk_select(s.astype(np.float64), min(h, n_keys), n_keys + w, w)), h
+
+
 @pytest.mark.parametrize("name", ["tiny_4f", "ragged_3f", "straddle_3f"])
 def test_vnorm_scores_and_selection_layers(name):
     """Eq. 3 / Eq. 4: several layers' V share one C; scores within fp32 rounding, kept sets exact outside the band."""
