@@ -97,6 +97,28 @@ void build_plan(purekv_plan& p, int n_cu) {
     const bool use_stack = stack && whole_stacks;
     g.Gs = use_stack ? gs : 1;
     g.R = use_stack ? r : kWaves;
+    // Few units: fewer wavefronts share a compute unit.  A SIMD with one wavefront takes three quarters of the time for a step
+    // that one with two takes, so half the row blocks, or half the heads, in a workgroup pay where every unit still has a
+    // compute unit of its own; going on to two wavefronts and one (shorter starts, a few %) where that leaves as many units
+    // idle for slices of long lists.  Prefill alone, eight wavefronts -> by this rule, dense / sparse, us: 288 tokens, 2/1
+    // heads of 64: 8.6 -> 6.8 / 8.1 -> 6.5; 452, 4/2 of 128: 15.1 -> 11.1 / 15.5 -> 11.2; 905, 8/2 of 128: 23.6 -> 17.8 / 22.3 -> 16.9;
+    // 900, 28/4 of 128: 25.4 -> 18.9 / as before (7 heads are not halved); 1088, 16/2 of 128: 26.4 -> 20.5 / 22.7 -> 17.6;
+    // 1796, 8/2 of 64: 20.4 -> 16.8 / 19.2 -> 16.3 (with two wavefronts 21.0 / 18.5).
+    // (Sparse plans keep two heads stacked, and those of single heads their eight row blocks: a plan over some heads lists the
+    // tiles of a plan of those heads alone.)
+    auto units = [&](int32_t gs1, int32_t r1) {
+      return int64_t((g.N + r1 * kBlockRows - 1) / (r1 * kBlockRows)) * (g.Hq / gs1);
+    };
+    const bool sparse = g.pattern != PUREKV_PATTERN_DENSE;
+    if (p.head_sel.empty() && !(sparse && g.G == 1))
+      while (g.Gs * g.R > 1) {
+        const bool rows = g.R % 2 == 0;
+        if (!rows && (g.Gs % 2 != 0 || (sparse && g.Gs == 2))) break;
+        const int32_t gs1 = rows ? g.Gs : g.Gs / 2, r1 = rows ? g.R / 2 : g.R;
+        if ((gs1 * r1 < kWaves / 2 ? 2 : 1) * units(gs1, r1) > n_cu) break;
+        g.Gs = gs1;
+        g.R = r1;
+      }
     g.n_groups = g.Hq / g.Gs;
   }
   auto group_selected = [&](int32_t grp) { return p.head_sel.empty() || p.head_sel[grp * g.Gs] != 0; };

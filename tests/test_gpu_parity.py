@@ -93,6 +93,41 @@ def test_prefill_matches_oracle(name, pattern):
         assert max(len(plan.queue(g)) for g in range(c["n_workgroups"])) >= 2  # some queue switches units
 
 
+@pytest.mark.parametrize("pattern", [0, 1, 2, 3])
+@pytest.mark.parametrize("name", list(SMALL))
+def test_prefill_workgroup_shapes(name, pattern):
+    """A shape with few units is planned with fewer wavefronts per workgroup, as far as every unit still has a compute unit.  The
+    same heads repeated until that ends: every shape on the way, the full one among them, against the oracle of the heads
+    themselves."""
+    wl = SMALL[name]
+    inp = generate(wl, seed=11)
+    q, k, v = to_dev(inp.q), to_dev(inp.k), to_dev(inp.v)
+    ref, ref_lse = orc.masked_attention(F64(inp.q), F64(inp.k), F64(inp.v), wl.n_frames, wl.patches, wl.n_text, pattern)
+    seen, times = set(), 1
+    while True:
+        hq, hkv = wl.n_q_heads * times, wl.n_kv_heads * times
+        plan = pk.Plan(wl.n_frames, wl.patch_h, wl.patch_w, wl.n_text, hq, hkv, wl.head_dim, pattern)
+        c = plan.counts()
+        shape = (c["stacked_heads"], c["row_blocks"])
+        n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+        lists = c["n_qtiles"] * c["n_head_groups"]
+        if shape not in seen:
+            print(f"[case] prefill {name} pattern={pattern} x{times} shape={shape}", flush=True)
+            assert shape[0] * shape[1] > 4 or lists <= n_cu
+            out, lse = pk.purekv_st_spattn_prefill(plan, *(x.repeat(times, 1, 1) for x in (q, k, v)), want_lse=True)
+            torch.cuda.synchronize()
+            for part in (0, times // 2, times - 1):
+                rows = slice(part * wl.n_q_heads, (part + 1) * wl.n_q_heads)
+                check_attention(f64_of(out[rows]), ref, f"{name}/p{pattern} x{times}")
+                assert np.abs(f64_of(lse[rows]) - ref_lse).max() < 2e-3
+        seen.add(shape)
+        plan.close()
+        if lists > 2 * n_cu:
+            break
+        times *= 2
+    assert any(a * b > 4 for a, b in seen)
+
+
 @pytest.mark.parametrize("want_lse", [False, True])
 @pytest.mark.parametrize("dim", [64, 128])
 @pytest.mark.parametrize("frames,patch_h,patch_w,text", [(2, 5, 5, 0), (2, 7, 7, 2), (3, 7, 8, 12)])
