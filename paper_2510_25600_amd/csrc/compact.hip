@@ -10,14 +10,15 @@ namespace {
 
 // grid = (row blocks, layers * Hkv).  Bound by two dependent trips to memory (index, rows) for one layer, by HBM for a stack.
 // (One axis over all rows took two 64-bit divisions per row ahead of them: 2.96 against 1.80 us for 57 rows of 64, 5.5 against
-// 5.3 for 1689 x 4 of 128, 31.4 against 31.0 for 26 layers of those.)
+// 5.3 for 1689 x 4 of 128, 31.4 against 31.0 for 26 layers of those.  Two rows in flight per lane and twice the workgroups of four:
+// 29.5 for the 26 layers; one: 29.0, but 2.1 for the 57 rows.)
 template <int D>
 __global__ __launch_bounds__(256) void compact_kernel(const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                                                       int64_t layer_stride, int64_t head_stride, int64_t tok_stride,
                                                       const int32_t* __restrict__ idx,
                                                       uint16_t* __restrict__ kc, uint16_t* __restrict__ vc, int32_t N,
                                                       int32_t Hkv, int32_t n_keep, int32_t cap) {
-  constexpr int LPR = D / 8, RPB = 256 / LPR, UNROLL = 4;
+  constexpr int LPR = D / 8, RPB = 256 / LPR, UNROLL = 2;
   const int sub = threadIdx.x % LPR, rslot = threadIdx.x / LPR;
   const int lk = blockIdx.y, layer = lk / Hkv, kvh = lk - layer * Hkv;
   const int64_t src0 = layer * layer_stride + kvh * head_stride + sub * 8;
@@ -64,7 +65,7 @@ __global__ void append_kernel(const uint16_t* __restrict__ k_new, const uint16_t
 int launch_compact(const purekv_plan& p, const void* k, const void* v, int64_t kv_layer_stride, int32_t n_layers,
                    const int32_t* idx, int32_t n_keep, void* kc, void* vc, int32_t cap, hipStream_t st) {
   if (n_keep == 0) return PUREKV_OK;
-  const int rows_per_block = (256 / (p.g.d / 8)) * 4;
+  const int rows_per_block = (256 / (p.g.d / 8)) * 2;
   const unsigned gx = (unsigned)((n_keep + rows_per_block - 1) / rows_per_block);
   // (a grid has 65535 blocks on its second axis: more heads than that go layer by layer, in as many launches as it takes)
   const int32_t layers_per_launch = std::max(1, 65535 / p.g.Hkv);

@@ -2,7 +2,7 @@
 // the recent window" (Sec. 3.1), batched over layers that share one C.
 //
 //   score kernel : S[l, kv, j] = C[kv, j] * ||V[l, kv, j, :]||_2.  Pure HBM stream over V: one 16-lane
-//                  group per row, 16-byte loads (8 rows in flight per group), fp32 sum of squares,
+//                  group per row, 16-byte loads (4 rows in flight per group), fp32 sum of squares,
 //                  fixed-order lane reduction.
 //   select kernel: one workgroup per (layer, KV head).  The h-th largest value is found exactly on the
 //                  order-preserving integer image of the fp32 scores by an MSB-first radix select (rows of up to
@@ -53,7 +53,9 @@ __device__ __forceinline__ float row_norm2(float ss) {
 }
 
 // grid = (row blocks, layers * Hkv): a workgroup streams SCORE_ROWS consecutive rows of one (layer, KV head).
-constexpr int SCORE_UNROLL = 8;
+// Rows in flight per lane: four, with twice the workgroups of eight.  One layer of 4608 x 8 rows of 128 5.5 -> 4.7 us, 16384 x 4 6.6 -> 5.8,
+// 8192 x 104 36.0 -> 34.1 (kernel trace); two: 36.9 for the last.
+constexpr int SCORE_UNROLL = 4;
 // Cross-lane primitives on the DPP path of the vector ALU (a few cycles each; the generic shuffles go through
 // the LDS crossbar, ~100 cycles a step with 16 wavefronts on the CU).
 // row_shr:n = 0x110 + n moves a value n lanes up within a row of 16 lanes; row_bcast:15 (0x142) hands lane 15 of
