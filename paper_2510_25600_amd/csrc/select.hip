@@ -54,7 +54,7 @@ __device__ __forceinline__ float row_norm2(float ss) {
 
 // grid = (row blocks, layers * Hkv): a workgroup streams SCORE_ROWS consecutive rows of one (layer, KV head).
 // Rows in flight per lane: four, with twice the workgroups of eight.  One layer of 4608 x 8 rows of 128 5.5 -> 4.7 us, 16384 x 4 6.6 -> 5.8,
-// 8192 x 104 36.0 -> 34.1 (kernel trace); two: 36.9 for the last.
+// 8192 x 104 36.0 -> 34.1 (kernel trace).  With two, the last and its compaction together take 73.7 instead of 70.9.
 constexpr int SCORE_UNROLL = 4;
 // Cross-lane primitives on the DPP path of the vector ALU (a few cycles each; the generic shuffles go through
 // the LDS crossbar, ~100 cycles a step with 16 wavefronts on the CU).
