@@ -24,8 +24,8 @@
 // in, output out) and one compute unit that pulled in all heads of the group; asking for the data itself leaves two and
 // spreads them over as many compute units as there are heads.  5491 keys x 4 KV heads x 7 query heads 9.9 -> 7.6 us a call,
 // 6900 keys 11.2 -> 8.8 (28 caches in turn), 1690 keys 8.7 -> 7.0, 10 000 keys x 8 KV heads x 4 17.8 -> 12.5.  (All eight
-// wavefronts asking for pairs and outputs from the start got in the way of the stores they were waiting for: 8.5.  Half of
-// the pairs, all of them, three quarters: 7.64, 7.76, 7.63.)
+// wavefronts asking for pairs and outputs from the start got in the way of the stores they were waiting for: 8.5.  4000
+// keys x 4 x 7, waiting for half of the pairs, all of them, three quarters: 7.64, 7.76, 7.63.)
 // With k_new/v_new given, row n_cached - 1 of the cache is taken from them instead of the cache and the workgroup
 // that owns that key also stores it there (append and attention in one pass over the cache).
 #include <algorithm>

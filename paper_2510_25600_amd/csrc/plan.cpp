@@ -101,7 +101,7 @@ void build_plan(purekv_plan& p, int n_cu) {
     // that one with two takes, so half the row blocks, or half the heads, in a workgroup pay where every unit still has a
     // compute unit of its own; going on to two wavefronts and one (shorter starts, a few %) where that leaves as many units
     // idle for slices of long lists.  Prefill alone, eight wavefronts -> by this rule, dense / sparse, us: 288 tokens, 2/1
-    // heads of 64: 8.6 -> 6.8 / 8.1 -> 6.5; 452, 4/2 of 128: 15.1 -> 11.1 / 15.5 -> 11.2; 905, 8/2 of 128: 23.6 -> 17.8 / 22.3 -> 16.9;
+    // heads of 64: 8.6 -> 6.8 / 8.1 -> 6.6; 452, 4/2 of 128: 15.1 -> 11.1 / 15.5 -> 11.4; 905, 8/2 of 128: 23.6 -> 17.8 / 22.3 -> 16.7;
     // 900, 28/4 of 128: 25.4 -> 18.9 / as before (7 heads are not halved); 1088, 16/2 of 128: 26.4 -> 20.5 / 22.7 -> 17.6;
     // 1796, 8/2 of 64: 20.4 -> 16.8 / 19.2 -> 16.3 (with two wavefronts 21.0 / 18.5).
     // (Sparse plans keep two heads stacked, and those of single heads their eight row blocks: a plan over some heads lists the

@@ -603,7 +603,7 @@ def test_decode_step_merges_many_chunks(hq, hkv, d, n0):
     (28, 4, 128, (57 * 128, 57 * 128 + 1)),  # 256 compute units hold 57 chunks per KV head beside 28 gathering workgroups
     (8, 8, 64, (31 * 256, 31 * 256 + 1, 64 * 512 + 1)),   # chunks of 256, then 512; a second pass over 65 chunks
     (300, 1, 64, (600,)),                   # more heads than compute units: 19 head blocks, the last with 12 heads
-    (5, 5, 128, (300,)),                    # more planes than one for the gathering workgroups would not help: one head each
+    (5, 5, 128, (300,)),                    # one query head a KV head: one gathering workgroup each
 ])
 def test_decode_gathers_chunks_of_every_size(hq, hkv, d, ns):
     """Chunks of 128, 256 and 512 keys, added up by the gathering workgroups or, where these never wait, by the last one: the
