@@ -186,16 +186,23 @@ __device__ __forceinline__ void block_scan2(uint32_t& a, uint32_t& b, uint32_t* 
 //
 // MSB-first radix select on the keys' distances from the smallest one, 12 bits a pass, LDS histogram of 4096 bins: a row's range
 // is some 14 octaves, so a bin of the first pass holds a 64th of an octave or so and the h-th largest key shares it with a
-// few dozen others.  SEL_LIST or fewer are ranked directly, one candidate a wavefront at a time.
+// few dozen others.  SEL_LIST or fewer are ranked directly, one candidate a wavefront at a time; more are looked at again from
+// the smallest of them on (a pass over the bin's own range would leave keys that are all equal, or nearly, together).
 //
 // A row is one workgroup's chain of barriers and LDS round trips and its 16 wavefronts' vector instructions on one CU; what
 // counts is how few of both there are.  The histogram has two buffers, the idle one is cleared behind the scan; ballots count
 // the kept keys of every 64 consecutive indices, and each wavefront scans the table of those counts by itself; a row without a
-// tie at the threshold needs one comparison a key for that, not two.  Log-normal scores x 4 KV heads between the other
-// kernels of a layer (kernel trace, median): 4199 6.9 -> 5.0 us, 8192 7.2 -> 6.2, 16384 10.9 -> 8.7; 8192 x 104 8.0 -> 6.4.  (Before:
-// digits of 8 bits of the keys as they are, which for scores about a power of 16 hold the exponent and little else, so two passes;
-// all wavefronts ranked all candidates.  Histogram in two copies of 2048 bins: 16384 9.3.  Lists of 128: no change.)
+// tie at the threshold needs one comparison a key for that, not two.  One histogram means that keys of one bin are added one
+// after the other, so crowded bins are counted apart.  us, 4 rows, calls one after the other, with digits of 8 bits and 16
+// copies of their histogram, with 4096 bins and nothing for crowds, now:
+//   scores              log-normal         nine in ten are 0    four values        all but one alike   three in ten are 0
+//   4199                6.7, 5.1, 4.8      8.0, 15.2, 5.6       7.8, 9.5, 5.7      7.8, 13.4, 7.3      6.7, 5.8, 5.5
+//   8192                7.5, 5.8, 5.3      9.2, 24.9, 6.6       8.6, 14.0, 7.4     8.7, 21.6, 8.7      7.6, 8.2, 7.9
+//   16384               11.7, 8.3, 7.7     14.3, 45.5, 9.8      13.0, 24.0, 12.0   13.3, 38.9, 13.4    11.2, 12.6, 11.5
+//   17000               15.8, 11.5, 10.5   19.5, 49.2, 14.7     18.3, 27.2, 15.6   18.6, 42.5, 20.0    15.9, 15.9, 16.4
+// (Histogram in two copies of 2048 bins: log-normal 16384 0.6 more.  Lists of 128: no change.)
 constexpr uint32_t SEL_LIST = 64;
+constexpr int CROWD = 6;   // of 64 lanes: 64 p^2 share a bin with lane ^ 1 where a fraction p of the keys is in one (12: "three in ten" 0.5 to 1.3 us more)
 // A layer's V of up to 128 KB per KV head (eight loads of 16 bytes per thread, all in flight together) is read by the selecting
 // workgroup itself: one round trip to memory instead of a launch, its drain and the scores' way through memory.  256 keys of 64:
 // 3.8 + 5.1 us in two launches, 4.0 in one.  Beyond that a single CU pulls the rows in slower than the chip does.
@@ -215,6 +222,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
   // different banks.
   constexpr int WAVES = SEL_THREADS / 64, HBITS = 12, HWORDS = 4096 + 4 * 64;
   constexpr int TPL = (EPT * WAVES + 63) / 64;   // entries of the table of counts per lane
+  constexpr int FULL = EPT == 1 ? 0 : EPT == 2 ? 1 : EPT == 4 ? 2 : EPT == 6 ? 4 : EPT == 8 ? 6 : EPT / 2;   // elements that every thread has (the next smaller width)
   static_assert(WAVES % TPL == 0, "entry e * WAVES + w is entry w % TPL of its lane");
   __shared__ __attribute__((aligned(16))) uint32_t hist[2][HWORDS];
   __shared__ __attribute__((aligned(16))) uint32_t counts[64 * TPL];   // [e][wavefront] kept keys: above | equal << 16
@@ -272,10 +280,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
 #pragma unroll
     for (int e = 0; e < EPT; ++e) raw[e] = sc[min(e * SEL_THREADS + tid, n_keys - 1)];
   }
-  // Keys are the scores' images less the smallest one, plus 1: the highest digit then tells apart what the row's range holds (of
-  // keys as they are it tells apart exponents and little else when these lie about a power of 16).  Elements past the end of
-  // the row (they were loaded as its last one) become key 0, below every score's: they are never among the h <= n_keys
-  // largest.
+  // Keys are the scores' images.  Elements past the end of the row (they were loaded as its last one) become key 0, below every
+  // score's: they are never among the h <= n_keys largest.
   uint32_t key[EPT];
   uint32_t kmin = 0xffffffffu, kmax = 0u;
 #pragma unroll
@@ -292,37 +298,59 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
   }
   __syncthreads();
   static_assert(WAVES == 16, "a row of 16 lanes holds the wavefronts'");
-  kmin = __builtin_amdgcn_readlane(row_scan_min(ext[0][lane & 15]), 15);
-  kmax = __builtin_amdgcn_readlane(row_scan_max(ext[1][lane & 15]), 15);
+  // Candidates for the h-th largest: the keys of [base, base + range], `remaining` of them are among the kept ones.
+  uint32_t base = __builtin_amdgcn_readlane(row_scan_min(ext[0][lane & 15]), 15);
+  uint32_t range = __builtin_amdgcn_readlane(row_scan_max(ext[1][lane & 15]), 15) - base;
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    key[e] -= kmin - 1u;
+  for (int e = FULL; e < EPT; ++e)
     if ((e + 1) * SEL_THREADS > n_keys) key[e] = e * SEL_THREADS + tid < n_keys ? key[e] : 0u;
-  }
-  // highest bit of a key; -1 when all are equal (to 1)
-  int top = kmax != kmin ? 31 - __clz((int)(kmax - kmin + 1u)) : -1;
-  uint32_t prefix = top < 0 ? 1u : 0u;
-  bool first_pass = true, all_ties = false;   // all_ties: every key equal to the h-th largest is kept
-  uint32_t remaining = (uint32_t)h;
+  uint32_t remaining = (uint32_t)h, n_cand = (uint32_t)n_keys;
+  bool first_pass = true;
   int buf = 0;
   auto word_of = [](uint32_t bin) { return bin + 4u * (bin >> 6); };
-  while (top >= 0) {
-    const int shift = max(top - (HBITS - 1), 0);
-    const uint32_t dmask = (2u << (top - shift)) - 1u;           // digit = bits top .. shift
-    // candidates behind the first pass: keys of [prefix, prefix + 2^(top + 1)), but not 0
-    const uint32_t lo = max(prefix, 1u), width = (2u << top) - (lo - prefix);
+  auto chosen = [&](int i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)sel[i]); };   // uniform: so are the branches on it
+  while (range != 0u) {
+    // digit = the highest HBITS bits of the distance from `base`
+    const int shift = max(32 - HBITS - __clz((int)range), 0);
     uint32_t* const my_hist = hist[buf];
-    if (first_pass) {   // every score is a candidate
+    // Keys crowded into one or two bins (weights that are exactly 0, few distinct values, one key far from all others): additions
+    // of a wavefront to one address are served a lane at a time, 130 cycles for 64 lanes.  Where many lanes share the bin of
+    // lane ^ 1, the bins of the first two that differ are counted in scalar registers.
+    const uint32_t bin0 = key[0] - base <= range ? (key[0] - base) >> shift : 0x10000u + (uint32_t)lane;
+    const uint64_t shared = __ballot(bin0 == (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bin0, 0xB1, 0xf, 0xf, false));
+    // (opaque: what the loops below have in common, and all that is the same in every pass, would be formed ahead of them for
+    // every element and kept in scalar registers that are not there)
+    uint32_t from = base;
+    int n_here = n_keys;
+    asm volatile("" : "+s"(from), "+s"(n_here));
+    if (EPT > 1 && __builtin_expect(__popcll(shared) >= CROWD, 0)) {
+      const uint32_t c0 = __builtin_amdgcn_readlane(bin0, __ffsll((unsigned long long)shared) - 1);
+      const uint64_t others = shared & __ballot(bin0 != c0);
+      const uint32_t c1 = others != 0 ? __builtin_amdgcn_readlane(bin0, __ffsll((unsigned long long)others) - 1) : c0;
+      uint32_t n0 = 0, n1 = 0;
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
-        const uint32_t u = key[e];
-        if ((e + 1) * SEL_THREADS <= n_keys || u != 0u) atomicAdd(&my_hist[word_of((u >> shift) & dmask)], 1u);
+        const uint32_t at = key[e] - from, bin = at >> shift;
+        const uint64_t in = __builtin_amdgcn_ballot_w64(at <= range), in0 = in & __builtin_amdgcn_ballot_w64(bin == c0),
+                       in1 = in & __builtin_amdgcn_ballot_w64(bin == c1);
+        n0 += (uint32_t)__popcll(in0);
+        n1 += (uint32_t)__popcll(in1);
+        asm volatile("" : "+s"(n0), "+s"(n1));   // (counted here: the masks of all elements do not fit the scalar registers)
+        if ((in & ~(in0 | in1)) >> lane & 1u) atomicAdd(&my_hist[word_of(bin)], 1u);
+      }
+      if (lane == 0) atomicAdd(&my_hist[word_of(c0)], n0);
+      if (lane == 1 && c1 != c0) atomicAdd(&my_hist[word_of(c1)], n1);
+    } else if (first_pass) {   // every score is a candidate
+#pragma unroll
+      for (int e = 0; e < EPT; ++e) {
+        const uint32_t at = key[e] - from;
+        if (e < FULL || (e + 1) * SEL_THREADS <= n_here || at <= range) atomicAdd(&my_hist[word_of(at >> shift)], 1u);
       }
     } else {
 #pragma unroll
       for (int e = 0; e < EPT; ++e) {
-        const uint32_t u = key[e];
-        if (u - lo < width) atomicAdd(&my_hist[word_of((u >> shift) & dmask)], 1u);
+        const uint32_t at = key[e] - from;
+        if (at <= range) atomicAdd(&my_hist[word_of(at >> shift)], 1u);
       }
     }
     first_pass = false;
@@ -350,18 +378,18 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
       for (int i = tid - 64; i < HWORDS; i += SEL_THREADS - 64) hist[buf ^ 1][i] = 0;
     }
     __syncthreads();
-    prefix |= sel[0] << shift;
-    remaining = sel[1];
-    const uint32_t n_cand = sel[2];
+    const uint32_t below = chosen(0) << shift;
+    base += below;
+    range = min(range - below, (1u << shift) - 1u);
+    remaining = chosen(1);
+    n_cand = chosen(2);
     buf ^= 1;
-    top = shift - 1;
-    all_ties = remaining == n_cand;   // (read behind the last pass)
-    if (top >= 0 && n_cand <= SEL_LIST) {
-      // few keys share the prefix: gather them (in any order) and rank them, a candidate a wavefront at a time
-      const uint32_t from = max(prefix, 1u), n_keys_of = (2u << top) - (from - prefix);
+    if (range == 0u) break;
+    if (n_cand <= SEL_LIST) {
+      // few keys share the digits: gather them (in any order) and rank them, a candidate a wavefront at a time
 #pragma unroll
       for (int e = 0; e < EPT; ++e)
-        if (key[e] - from < n_keys_of) list[atomicAdd(&list_n, 1u)] = key[e];   // n_cand of them
+        if (key[e] - base <= range) list[atomicAdd(&list_n, 1u)] = key[e];   // n_cand of them
       __syncthreads();
       const uint32_t other = lane < (int)n_cand ? list[lane] : 0u;   // (below every candidate)
       for (int i = wave; i < (int)n_cand; i += WAVES) {
@@ -374,14 +402,32 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
         }
       }
       __syncthreads();
-      prefix = sel[0];
-      remaining = sel[1];
-      all_ties = remaining == sel[2];
+      base = chosen(0);
+      remaining = chosen(1);
+      n_cand = chosen(2);
       break;
     }
+    // Many keys share them: their own range, which is 0 for a row of few distinct values, instead of the bin's.
+    uint32_t cmin = 0xffffffffu, cmax = 0u;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+      if (key[e] - base <= range) {
+        cmin = min(cmin, key[e]);
+        cmax = max(cmax, key[e]);
+      }
+    cmin = wave_scan_min(cmin);
+    cmax = wave_scan_max(cmax);
+    if (lane == 63) {
+      ext[0][wave] = cmin;
+      ext[1][wave] = cmax;
+    }
+    __syncthreads();
+    base = __builtin_amdgcn_readlane(row_scan_min(ext[0][lane & 15]), 15);
+    range = __builtin_amdgcn_readlane(row_scan_max(ext[1][lane & 15]), 15) - base;
   }
-  // prefix = key of the h-th largest score; `remaining` of the keys equal to it are kept (lowest indices)
-  const uint32_t tau = prefix, need = remaining;
+  // base = key of the h-th largest score; `remaining` of the n_cand keys equal to it are kept (lowest indices)
+  const uint32_t tau = base, need = remaining;
+  const bool all_ties = remaining == n_cand;   // every one of them is
   // With no tie to break (nearly always), a kept key is one that is not less than tau: one comparison, one rank.
   uint32_t mine = 0;   // lane e: counts of this wavefront's element e
   if (all_ties) {
@@ -408,17 +454,17 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
     ent[i] = counts[lane * TPL + i];
     tot += ent[i];
   }
-  uint32_t base = wave_scan_add(tot) - tot;
+  uint32_t ahead = wave_scan_add(tot) - tot;
 #pragma unroll
-  for (int i = 0; i < TPL - 1; ++i) base += i < wave % TPL ? ent[i] : 0u;
+  for (int i = 0; i < TPL - 1; ++i) ahead += i < wave % TPL ? ent[i] : 0u;
   auto rank = [](uint64_t m, uint32_t before) {   // of the lane among those of m
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, before));
   };
   if (all_ties) {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-      if (e * SEL_THREADS >= n_keys) break;
-      const uint32_t b = __builtin_amdgcn_readlane(base, (e * WAVES + wave) / TPL);
+      if (e >= FULL && e * SEL_THREADS >= n_keys) break;
+      const uint32_t b = __builtin_amdgcn_readlane(ahead, (e * WAVES + wave) / TPL);
       const bool kept = key[e] >= tau;
       const uint32_t at = rank(__ballot(kept), b);
       if (kept) out[at] = e * SEL_THREADS + tid;
@@ -426,8 +472,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(const float* __rest
   } else {
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
-      if (e * SEL_THREADS >= n_keys) break;
-      const uint32_t b = __builtin_amdgcn_readlane(base, (e * WAVES + wave) / TPL);
+      if (e >= FULL && e * SEL_THREADS >= n_keys) break;
+      const uint32_t b = __builtin_amdgcn_readlane(ahead, (e * WAVES + wave) / TPL);
       const bool is_gt = key[e] > tau, is_eq = key[e] == tau;
       const uint32_t gt = rank(__ballot(is_gt), b & 0xffffu), eq = rank(__ballot(is_eq), b >> 16);
       if (is_gt || (is_eq && eq < need)) out[gt + min(eq, need)] = e * SEL_THREADS + tid;
@@ -647,6 +693,9 @@ static int launch_select(const purekv_plan& p, const float* scores, int32_t n_la
   const dim3 sgrid((unsigned)(n_layers * p.g.Hkv)), sblock(SEL_THREADS);
   const int per_thread = (n_keys + SEL_THREADS - 1) / SEL_THREADS;
   auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, sgrid, sblock, 0, st, scores, ScoreArgs{}, idx_out, p.g.N, w, h); };
+  // A row takes little less than the longest one of its width: 4199 and 6144 log-normal scores 4.8 and 4.9 us, 8192 5.3; 9000 and
+  // 16384 6.9 and 7.7; 17000 and 32768 10.5 and 12.2 (so widths between the last three would save rows just above 8192 and 16384
+  // a us or two; there are none).
   if (per_thread <= 1)
     launch(select_kernel<1, 0>);
   else if (per_thread <= 2)

@@ -478,6 +478,57 @@ def test_topk_exact_on_scores_of_any_range(n_keys):
         assert np.array_equal(idx.cpu().numpy(), orc.topk_select(s.astype(np.float64), min(h, n_keys), n_keys + w, w)), h
 
 
+def _graph_us(call, calls=20):
+    """Median time of a call, us, of `calls` in a row from a HIP graph (no host in between)."""
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        call()
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for _ in range(calls):
+            call()
+    times = []
+    for _ in range(9):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / calls)
+    return sorted(times)[len(times) // 2]
+
+
+@pytest.mark.parametrize("n_keys", [1025, 4097, 8192, 16384, 16385])
+def test_selection_of_crowded_rows(n_keys):
+    """Rows whose keys share a bin or two of the histogram: weights that are exactly 0 (the threshold among them, above them),
+    four values, all but one within a few units in the last place, and those beside a spread.  Exact, and for the longer rows not
+    much slower than rows that spread out: additions of a wavefront to one bin, one lane at a time, took four to six times as long
+    (now 1.2 to 1.9)."""
+    w, rng = 7, np.random.default_rng(n_keys)
+    spread = np.exp(1.2 * rng.standard_normal(n_keys)).astype(np.float32)
+    zeros = np.where(rng.random(n_keys) < 0.9, np.float32(0), spread)
+    alike = (np.float32(1.5).view(np.uint32) + rng.integers(0, 8, n_keys).astype(np.uint32)).view(np.float32)
+    alike[n_keys // 2] = 1e30
+    rows = {"spread": spread, "zeros": zeros, "four values": rng.integers(1, 5, n_keys).astype(np.float32), "alike": alike,
+            "alike and spread": np.where(rng.random(n_keys) < 0.4, alike, spread), "-zeros": -zeros}
+    plan, one = pk.Plan(1, 1, n_keys, w, len(rows), len(rows), 64, 0), pk.Plan(1, 1, n_keys, w, 4, 4, 64, 0)
+    s = np.stack(list(rows.values()))
+    for h in (1, n_keys // 20, n_keys // 10, n_keys // 5, n_keys // 2, n_keys - 1):
+        idx = pk.purekv_topk_select(plan, torch.from_numpy(s).cuda(), None, w, h)
+        assert np.array_equal(idx.cpu().numpy(), orc.topk_select(s.astype(np.float64), h, n_keys + w, w)), h
+    if n_keys < 8192:
+        return
+    times = {}
+    for name, row in rows.items():
+        c = torch.from_numpy(np.stack([row] * 4)).cuda()
+        out = torch.empty((1, 4, n_keys // 5 + w), dtype=torch.int32, device="cuda")
+        times[name] = _graph_us(lambda: pk.purekv_topk_select(one, c, None, w, n_keys // 5, idx_out=out))
+    print(f"[case] {n_keys} keys, us: {times}", flush=True)
+    assert max(times.values()) <= 2.5 * times["spread"], times
+
+
 @pytest.mark.parametrize("name", ["tiny_4f", "ragged_3f", "straddle_3f"])
 def test_vnorm_scores_and_selection_layers(name):
     """Eq. 3 / Eq. 4: several layers' V share one C; scores within fp32 rounding, kept sets exact outside the band."""
