@@ -1187,6 +1187,29 @@ def test_prefill_emits_squared_v_norms(name, pattern):
         check_kept_sets(idx.cpu().numpy(), orc.topk_select(s_ref, h, n, w), s_ref, h)
 
 
+@pytest.mark.parametrize("hq,hkv,d,frames,patch,text,pattern", [
+    (16, 2, 128, 8, 10, 96, 0), (8, 8, 128, 8, 17, 100, 0), (32, 8, 128, 8, 10, 96, 3), (4, 2, 64, 8, 10, 96, 3)])
+def test_v_norms_cost_a_short_pass_where_few_wavefronts_have_rows(hq, hkv, d, frames, patch, text, pattern):
+    """Plans of four wavefronts or fewer a workgroup take the norms from a pass over V (2.3 us here), not from the launch, whose
+    steps wait for them there (12 to 18 us with heads of 128); bit for bit the norms that any such plan's call gives."""
+    plan = pk.Plan(frames, patch, patch, text, hq, hkv, d, pattern)
+    n, c = plan.N, plan.counts()
+    assert c["stacked_heads"] * c["row_blocks"] <= pk.WAVES // 2
+    gen = torch.Generator(device="cuda").manual_seed(n + hq)
+    q, k, v = (torch.randn((x, n, d), generator=gen, device="cuda").bfloat16() for x in (hq, hkv, hkv))
+    out, n2 = plan.empty_out("cuda"), torch.full((hkv, n), float("nan"), dtype=torch.float32, device="cuda")
+    plain = _graph_us(lambda: pk.purekv_st_spattn_prefill(plan, q, k, v, out=out))
+    norms = _graph_us(lambda: pk.purekv_st_spattn_prefill(plan, q, k, v, out=out, vnorm2=n2))
+    print(f"[case] {hq}/{hkv} heads of {d}, {n} tokens: {plain:.1f} us, with norms {norms:.1f}", flush=True)
+    assert norms <= plain + 7.0
+    eight = pk.Plan(1, 1, 1, n - 1, 512, hkv, d, 0)   # eight wavefronts: a pass of its own as well
+    assert eight.counts()["stacked_heads"] * eight.counts()["row_blocks"] == pk.WAVES
+    ref = torch.full_like(n2, float("nan"))
+    big = torch.zeros((512, n, d), dtype=torch.bfloat16, device="cuda")
+    pk.purekv_st_spattn_prefill(eight, big, k, v, vnorm2=ref)
+    assert torch.equal(n2.view(torch.int32), ref.view(torch.int32))
+
+
 def test_prefill_vnorm_layers_and_head_subsets():
     """Layered norms [L, Hkv, N] through one batched selection, and a plan over a head subset: the KV heads none of
     whose query heads it covers keep what the buffer held."""
