@@ -68,59 +68,11 @@ inline int32_t largest_divisor_up_to(int32_t g, int32_t cap) {
   return 1;
 }
 
-}  // namespace
-
-void build_plan(purekv_plan& p, int n_cu) {
+// Lists, schedule and steps of a plan whose workgroup shape (Gs, R, n_groups) is given; returns the model's prediction of when
+// its last workgroup ends, in steps of a plain tile.
+double build_shape(purekv_plan& p, int n_cu) {
   Geometry& g = p.g;
   const int32_t BK = PUREKV_BK;
-  p.n_cu = n_cu;
-
-  // ---- workgroup shape ----
-  // Stacking the query heads of a KV group in one workgroup makes every wavefront of the workgroup need the
-  // same key tiles (the mask depends on the row, not on the head), so nobody waits at the tile barriers for
-  // work it does not share.  The dense pattern has little such imbalance (only the diagonal tiles): it stacks
-  // only when that fills all wavefronts, else one head x 8 row blocks keeps every SIMD busy.
-  {
-    const int32_t gs = largest_divisor_up_to(g.G, kWaves), r = kWaves / gs;
-    const bool stack = (g.pattern != PUREKV_PATTERN_DENSE && gs >= 2) || (gs * r == kWaves && gs >= 2);
-    // A head subset keeps the stacked shape when it is made of whole stacks (e.g. whole KV groups); otherwise it is
-    // planned head by head.
-    bool whole_stacks = true;
-    p.n_heads_sel = g.Hq;
-    if (!p.head_sel.empty()) {
-      p.n_heads_sel = 0;
-      for (int32_t hq = 0; hq < g.Hq; ++hq) {
-        p.n_heads_sel += p.head_sel[hq] != 0;
-        whole_stacks &= (p.head_sel[hq] != 0) == (p.head_sel[hq - hq % gs] != 0);
-      }
-    }
-    const bool use_stack = stack && whole_stacks;
-    g.Gs = use_stack ? gs : 1;
-    g.R = use_stack ? r : kWaves;
-    // Few units: fewer wavefronts share a compute unit.  A SIMD with one wavefront takes three quarters of the time for a step
-    // that one with two takes, so half the row blocks, or half the heads, in a workgroup pay where every unit still has a
-    // compute unit of its own; going on to two wavefronts and one (shorter starts, a few %) where that leaves as many units
-    // idle for slices of long lists.  Prefill alone, eight wavefronts -> by this rule, dense / sparse, us: 288 tokens, 2/1
-    // heads of 64: 8.6 -> 6.8 / 8.1 -> 6.6; 452, 4/2 of 128: 15.1 -> 11.1 / 15.5 -> 11.4; 905, 8/2 of 128: 23.6 -> 17.8 / 22.3 -> 16.7;
-    // 900, 28/4 of 128: 25.4 -> 18.9 / as before (7 heads are not halved); 1088, 16/2 of 128: 26.4 -> 20.5 / 22.7 -> 17.6;
-    // 1796, 8/2 of 64: 20.4 -> 16.8 / 19.2 -> 16.3 (with two wavefronts 21.0 / 18.5).
-    // (Sparse plans keep two heads stacked, and those of single heads their eight row blocks: a plan over some heads lists the
-    // tiles of a plan of those heads alone.)
-    auto units = [&](int32_t gs1, int32_t r1) {
-      return int64_t((g.N + r1 * kBlockRows - 1) / (r1 * kBlockRows)) * (g.Hq / gs1);
-    };
-    const bool sparse = g.pattern != PUREKV_PATTERN_DENSE;
-    if (p.head_sel.empty() && !(sparse && g.G == 1))
-      while (g.Gs * g.R > 1) {
-        const bool rows = g.R % 2 == 0;
-        if (!rows && (g.Gs % 2 != 0 || (sparse && g.Gs == 2))) break;
-        const int32_t gs1 = rows ? g.Gs : g.Gs / 2, r1 = rows ? g.R / 2 : g.R;
-        if ((gs1 * r1 < kWaves / 2 ? 2 : 1) * units(gs1, r1) > n_cu) break;
-        g.Gs = gs1;
-        g.R = r1;
-      }
-    g.n_groups = g.Hq / g.Gs;
-  }
   auto group_selected = [&](int32_t grp) { return p.head_sel.empty() || p.head_sel[grp * g.Gs] != 0; };
   const int32_t n_groups_sel = p.n_heads_sel / g.Gs;
   const int32_t rows_per_qtile = g.R * kBlockRows;
@@ -577,6 +529,80 @@ void build_plan(purekv_plan& p, int n_cu) {
     p.queue_units_begin.push_back(static_cast<int32_t>(p.queue_units.size() / 2));
   }
   p.units.push_back(Unit{});  // spare record: the kernel fetches the record after the current unit unconditionally
+  return chosen.end;
+}
+
+}  // namespace
+
+void build_plan(purekv_plan& p, int n_cu) {
+  Geometry& g = p.g;
+  p.n_cu = n_cu;
+  // Stacking the query heads of a KV group in one workgroup makes every wavefront of the workgroup need the
+  // same key tiles (the mask depends on the row, not on the head), so nobody waits at the tile barriers for
+  // work it does not share.  The dense pattern has little such imbalance (only the diagonal tiles): it stacks
+  // only when that fills all wavefronts, else one head x 8 row blocks keeps every SIMD busy.
+  const bool sparse = g.pattern != PUREKV_PATTERN_DENSE;
+  const int32_t gs = largest_divisor_up_to(g.G, kWaves), r = kWaves / gs;
+  const bool stack = (sparse && gs >= 2) || (gs * r == kWaves && gs >= 2);
+  // A head subset keeps the stacked shape when it is made of whole stacks (e.g. whole KV groups); otherwise it is
+  // planned head by head.
+  bool whole_stacks = true;
+  p.n_heads_sel = g.Hq;
+  if (!p.head_sel.empty()) {
+    p.n_heads_sel = 0;
+    for (int32_t hq = 0; hq < g.Hq; ++hq) {
+      p.n_heads_sel += p.head_sel[hq] != 0;
+      whole_stacks &= (p.head_sel[hq] != 0) == (p.head_sel[hq - hq % gs] != 0);
+    }
+  }
+  auto build = [&](int32_t gs1, int32_t r1) {
+    g.Gs = gs1;
+    g.R = r1;
+    g.n_groups = g.Hq / gs1;
+    return build_shape(p, n_cu);
+  };
+  const bool use_stack = stack && whole_stacks;
+  int32_t Gs = use_stack ? gs : 1, R = use_stack ? r : kWaves;
+
+  // Few units: fewer wavefronts share a compute unit.  A SIMD with one wavefront takes about 0.7 of the time for a step that one
+  // with two takes, so half the row blocks, or half the heads, in a workgroup pay where compute units would be idle otherwise;
+  // going on to two wavefronts and one (shorter starts, a few %) where half of them still would.  Where every compute unit has
+  // plenty of steps either way (slices of the long lists fill them) the same work in twice the steps is slower: up to 15 steps
+  // a compute unit the halves are taken, beyond that only halves of eight wavefronts that end sooner by the model.
+  // Prefill alone, dense, us, eight wavefronts -> four, steps a compute unit with four: 8/2 heads of 128, 1327 tokens (3.4) 26.4 ->
+  // 21.4; 16/2 of 128, 1990 (15) 35.8 -> 32.1; 8/8 of 64, 2896 (16) 26.2 -> 28.3; 8/8 of 128, 3279 (20) 39.8 -> 46.8; 4/2 of 64, 5203
+  // (26) 34.8 -> 43.2; and 2/1 of 64, 5792 (16) 31.6 -> 27.7, by the model.  Four -> two: 2/1 of 128, 2793 (7) 26.5 -> 26.1, 4579
+  // (20) 32.4 -> 46.6.  535 plans of 318 shapes: 0.884 of eight wavefronts' time (0.904 without the limit, 51 slower than with
+  // eight by more than 3 %, up to 1.37; now four: 1.06 and 1.08, 1448 tokens, 16/2, and 1.10 and 1.23, 3946 sparse, 4/2).
+  // (Sparse plans keep two heads stacked.  Left out and not measured with fewer wavefronts: head subsets, and the sparse plans of
+  // one head per KV head that a subset of single heads shares its lists with at any number of workgroups.)
+  if (p.head_sel.empty() && !(sparse && g.G == 1)) {
+    double pairs = -1;   // allowed pairs of a head
+    auto steps = [&](int32_t waves) {   // a compute unit's share of the steps, partly used ones left out
+      if (pairs < 0) {
+        pairs = 0;
+        for (int32_t i = 0; i < g.N; ++i) pairs += row_pairs(row_set(g, i), i);
+      }
+      return pairs * g.Hq / (double(waves) * kBlockRows * PUREKV_BK * n_cu);
+    };
+    constexpr double kFewSteps = 15.0;
+    const double kAloneCost = g.d == 128 ? 0.68 : 0.70;   // of a step, with one wavefront a SIMD
+    while (Gs * R > 1) {
+      const bool rows = R % 2 == 0;
+      if (!rows && (Gs % 2 != 0 || (sparse && Gs == 2))) break;
+      const int32_t gs1 = rows ? Gs : Gs / 2, r1 = rows ? R / 2 : R, waves = gs1 * r1;
+      const int64_t units = int64_t((g.N + r1 * kBlockRows - 1) / (r1 * kBlockRows)) * (g.Hq / gs1);
+      if ((waves < kWaves / 2 ? 2 : 1) * units > n_cu) break;
+      if (steps(waves) > kFewSteps) {
+        if (Gs * R <= kWaves / 2) break;
+        const double end = build(Gs, R);
+        if (kAloneCost * build(gs1, r1) >= end) break;
+      }
+      Gs = gs1;
+      R = r1;
+    }
+  }
+  (void)build(Gs, R);
 }
 
 }  // namespace purekv

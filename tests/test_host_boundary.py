@@ -438,6 +438,22 @@ def test_searching_a_schedule_costs_little_beside_listing_the_tiles():
     assert min(t[1] for t in tries) <= 2.0 * min(t[0] for t in tries)
 
 
+@pytest.mark.parametrize("heads,dim,tokens,waves", [
+    ((8, 2), 128, 1327, 4), ((16, 2), 128, 1990, 4), ((8, 8), 128, 2804, 4),   # up to 15 steps a compute unit: halves
+    ((8, 8), 64, 2896, 8), ((8, 8), 128, 3279, 8), ((8, 2), 64, 3238, 8), ((4, 2), 64, 5203, 8), ((4, 1), 128, 5608, 8),
+    ((2, 1), 128, 7931, 8), ((1, 1), 128, 11217, 8),                           # more: not, where the lists' slices fill the chip
+    ((2, 1), 64, 5792, 4), ((1, 1), 128, 8688, 4),                             # more, but eight wavefronts end later by the model
+    ((2, 1), 128, 2793, 2), ((2, 1), 128, 4579, 4), ((1, 1), 64, 7931, 4),     # a second halving: up to 15 steps only
+    ((28, 4), 128, 8448, 8)])
+def test_workgroups_shrink_only_where_compute_units_would_be_idle(heads, dim, tokens, waves):
+    """Wavefronts with rows of dense plans on 256 compute units: fewer where units are few, not where each compute unit has
+    many steps either way (half the wavefronts take twice the steps at 0.7 of the time)."""
+    plan = pk.Plan(1, 1, tokens - 64, 64, heads[0], heads[1], dim, pk.PATTERN_DENSE, host_only=True)
+    c = plan.counts()
+    plan.close()
+    assert c["stacked_heads"] * c["row_blocks"] == waves
+
+
 def test_window_plan_argument_errors():
     lib = pk.raw()
     shape = pk.Shape(4, 8, 8, 32, 4, 2, 64, 3, 0.0, 0, 0, 0, 0, 0, 0)
