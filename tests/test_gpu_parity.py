@@ -1191,7 +1191,8 @@ def test_prefill_emits_squared_v_norms(name, pattern):
     (16, 2, 128, 8, 10, 96, 0), (8, 8, 128, 8, 17, 100, 0), (32, 8, 128, 8, 10, 96, 3), (4, 2, 64, 8, 10, 96, 3)])
 def test_v_norms_cost_a_short_pass_where_few_wavefronts_have_rows(hq, hkv, d, frames, patch, text, pattern):
     """Plans of four wavefronts or fewer a workgroup take the norms from a pass over V (2.3 us here), not from the launch, whose
-    steps wait for them there (12 to 18 us with heads of 128); bit for bit the norms that any such plan's call gives."""
+    steps wait for them there (12 to 18 us with heads of 128); bit for bit the norms that any such plan's call gives.  With heads of
+    64 and three wavefronts or fewer the launch emits them (0 to 3 us); their sums are added up in another order."""
     plan = pk.Plan(frames, patch, patch, text, hq, hkv, d, pattern)
     n, c = plan.N, plan.counts()
     assert c["stacked_heads"] * c["row_blocks"] <= pk.WAVES // 2
@@ -1207,7 +1208,9 @@ def test_v_norms_cost_a_short_pass_where_few_wavefronts_have_rows(hq, hkv, d, fr
     ref = torch.full_like(n2, float("nan"))
     big = torch.zeros((512, n, d), dtype=torch.bfloat16, device="cuda")
     pk.purekv_st_spattn_prefill(eight, big, k, v, vnorm2=ref)
-    assert torch.equal(n2.view(torch.int32), ref.view(torch.int32))
+    if d == 128:
+        assert torch.equal(n2.view(torch.int32), ref.view(torch.int32))
+    assert ((n2 - ref).abs() <= 64 * 2 ** -24 * ref).all()   # at most d additions, each within an ulp, of squares
 
 
 def test_prefill_vnorm_layers_and_head_subsets():
