@@ -148,12 +148,17 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
       if (lane < nsb) ml = load_device_8(mlb, (uint32_t)(s0 + lane) * 8u);
     };
     auto pair_there = [&]() { return __float_as_uint(ml[0]) != 0u && __float_as_uint(ml[1]) != 0u; };
+    // The loads of a look are ordinary ones to the compiler, of addresses that do not change: without a barrier ahead of each look
+    // it may load once and look at the same registers until the looks are used up.
+    auto memory_has_changed = []() { asm volatile("" ::: "memory"); };
     for (;;) {
+      memory_has_changed();
       load_pairs();
       if (__popcll(__ballot(pair_there())) >= 64 - nsb / 2 || --polls <= 0) break;
       __builtin_amdgcn_s_sleep(1);
     }
     while (polls > 0) {
+      memory_has_changed();
       load_pairs();
 #pragma unroll
       for (int u = 0; u < U; ++u) {

@@ -622,16 +622,53 @@ def test_plan_lists_match_oracle_mask_random_shapes():
         _check_plan_against_oracle(F, ph, pw, T, hkv * g, hkv, 64, pattern, n_wg=int(rng.choice([3, 16, 256])))
 
 
+def _build_module():
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("_purekv_build", os.path.join(ROOT, "paper_2510_25600_amd", "build.py"))
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
+def test_every_look_at_partial_results_loads_them_again(tmp_path):
+    """Decode's gathering workgroups look at memory until other workgroups have written it, with loads that the compiler takes for
+    ordinary ones.  In its own intermediate code of every decode kernel, no device-scope load may reach itself without a
+    compiler barrier on the way."""
+    import subprocess
+    build = _build_module()
+    ir = tmp_path / "decode.ll"
+    subprocess.run([build.HIPCC, *build.FLAGS, "-x", "hip", "--offload-device-only", "-S", "-emit-llvm",
+                    os.path.join(build.CSRC, "decode.hip"), "-o", str(ir)], check=True, stderr=subprocess.DEVNULL)
+    kernels = re.findall(r"^define [^@]*@(\S*decode_kernelI\S*)\(.*?\{\n(.*?)^\}", ir.read_text(), re.M | re.S)
+    assert len(kernels) == 6
+    for name, body in kernels:
+        edges, loads, at = {}, [], ("", 0)   # a node is what lies between two barriers of a basic block
+        for line in body.splitlines():
+            if label := re.match(r"(\S+):", line):
+                at = (label.group(1), 0)
+            elif "asm sideeffect" in line and "~{memory}" in line:
+                at = (at[0], at[1] + 1)
+            elif re.search(r"raw\.ptr\.buffer\.load.*i32 16\)", line):
+                loads.append(at)
+            else:
+                edges.setdefault(at, set()).update((x, 0) for x in re.findall(r"\blabel %([\w.]+)", line))
+        assert loads
+        for load in loads:
+            seen, todo = set(), list(edges.get(load, ()))
+            while todo:
+                node = todo.pop()
+                if node not in seen:
+                    seen.add(node)
+                    todo += edges.get(node, ())
+            assert load not in seen, f"{name}: block {load[0]}"
+
+
 def test_host_code_under_address_and_undefined_behaviour_sanitizers():
     """The planner (346 lines of index arithmetic that size device tables) and the C ABI's host half, rebuilt with
     ASan + UBSan on the host side and driven over ~2000 shapes by tests/host_sanitizer_driver.cpp: any report or failed
     structural check makes the driver exit non-zero."""
-    import importlib.util
     import subprocess
-    spec = importlib.util.spec_from_file_location("_purekv_build", os.path.join(ROOT, "paper_2510_25600_amd", "build.py"))
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
-    exe = mod.build_host_sanitized(verbose=False)
+    exe = _build_module().build_host_sanitized(verbose=False)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0", UBSAN_OPTIONS="print_stacktrace=1")
     run = subprocess.run([exe], capture_output=True, text=True, timeout=600, env=env)
     assert run.returncode == 0, run.stdout[-2000:] + run.stderr[-4000:]
