@@ -308,11 +308,6 @@ PUREKV_API int purekv_decode_step(const purekv_plan_t* plan, const void* q_new, 
                                   void* kc, void* vc, int32_t n_cached, int32_t cap, void* out, void* ws,
                                   size_t ws_bytes, void* stream);
 
-/* How often the workgroups that add up the chunks of a decode call look for partial results that are not there yet before
- * they leave them to the last workgroup of the launch (each look takes half a microsecond): 0, never wait; negative, the
- * default.  The results are the same bit for bit.  Not while calls on the plan are being made. */
-PUREKV_API int purekv_plan_set_decode_polls(purekv_plan_t* plan, int32_t polls);
-
 /*
  * Layer stack (Sec. 3.1 and the layer-index study of the hyperparameter analysis, Sec. 4.5): which layer runs which attention and whose
  * importance estimate drives whose selection.

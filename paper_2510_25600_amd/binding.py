@@ -62,7 +62,6 @@ def _load() -> ctypes.CDLL:
         "purekv_plan_qtile_list": (c_int, [P, c_int32, POINTER(c_int32), c_int32]),
         "purekv_plan_item": (c_int, [P, c_int32, POINTER(c_int32)]),
         "purekv_plan_queue": (c_int, [P, c_int32, POINTER(c_int32), c_int32]),
-        "purekv_plan_set_decode_polls": (c_int, [P, c_int32]),
         "purekv_plan_steps": (c_int, [P, c_int32, POINTER(c_int32), c_int32]),
         "purekv_spearman": (c_int, [P, P, c_int32, c_int32, P, P, P]),
         "purekv_workspace_bytes": (c_size_t, [P, c_int, c_int32, c_int32, c_int32]),
@@ -104,7 +103,7 @@ EXPORTS = (
     "purekv_plan_qtile_list", "purekv_plan_item", "purekv_plan_queue", "purekv_plan_steps", "purekv_spearman", "purekv_workspace_bytes", "purekv_workspace_init",
     "purekv_stack_workspace_init", "purekv_st_spattn_prefill", "purekv_st_spattn_prefill_vnorm", "purekv_topk_select_vnorm",
     "purekv_lowlayer_importance", "purekv_topk_select", "purekv_topk_select_static", "purekv_kv_compact", "purekv_kv_append",
-    "purekv_decode_attn", "purekv_decode_step", "purekv_plan_set_decode_polls", "purekv_stack_workspace_bytes", "purekv_stack_layer",
+    "purekv_decode_attn", "purekv_decode_step", "purekv_stack_workspace_bytes", "purekv_stack_layer",
     "purekv_stack_select_compact", "purekv_budget", "purekv_plan_kept_tile_flops", "purekv_plan_mask_flops",
     "purekv_calib_mfma", "purekv_calib_mfma_flops", "purekv_calib_tile_step", "purekv_calib_tile_step_flops",
     "purekv_strerror",
@@ -287,9 +286,6 @@ class Plan:
         buf = (c_int32 * 6)()
         _check(_lib.purekv_plan_item(self._h, it, buf), "purekv_plan_item")
         return tuple(buf)
-
-    def set_decode_polls(self, polls: int) -> None:
-        _check(_lib.purekv_plan_set_decode_polls(self._h, polls), "purekv_plan_set_decode_polls")
 
     def kept_tile_flops(self) -> float:
         return float(_lib.purekv_plan_kept_tile_flops(self._h))

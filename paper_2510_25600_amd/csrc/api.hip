@@ -6,6 +6,7 @@
 #include <new>
 
 #include "common.h"
+#include "testing.h"
 
 namespace purekv {
 
@@ -384,11 +385,16 @@ int purekv_kv_append(const purekv_plan_t* p, const void* k_new, const void* v_ne
 
 int purekv_decode_attn(const purekv_plan_t* p, const void* q_new, const void* kc, const void* vc, int32_t n_cached,
                        int32_t cap, void* out, void* ws, size_t ws_bytes, void* stream) {
+  return purekv_testing_decode_attn(p, q_new, kc, vc, n_cached, cap, out, ws, ws_bytes, kDecodeLooks, stream);
+}
+
+int purekv_testing_decode_attn(const purekv_plan_t* p, const void* q_new, const void* kc, const void* vc, int32_t n_cached,
+                               int32_t cap, void* out, void* ws, size_t ws_bytes, int32_t looks, void* stream) {
   if (!launchable(p) || q_new == nullptr || kc == nullptr || vc == nullptr || out == nullptr) return PUREKV_EINVAL;
-  if (n_cached < 1 || n_cached > cap) return PUREKV_EINVAL;
+  if (n_cached < 1 || n_cached > cap || looks < 0) return PUREKV_EINVAL;
   if (ws == nullptr || ws_bytes < decode_ws_bytes(*p, cap)) return PUREKV_EWORKSPACE;
   return launch_decode(*p, q_new, nullptr, nullptr, const_cast<void*>(kc), const_cast<void*>(vc), n_cached, cap, out, ws,
-                       static_cast<hipStream_t>(stream));
+                       std::min(looks, kDecodeLooks), static_cast<hipStream_t>(stream));
 }
 
 int purekv_decode_step(const purekv_plan_t* p, const void* q_new, const void* k_new, const void* v_new, void* kc,
@@ -398,13 +404,7 @@ int purekv_decode_step(const purekv_plan_t* p, const void* q_new, const void* k_
     return PUREKV_EINVAL;
   if (n_cached < 0 || n_cached >= cap) return PUREKV_EINVAL;
   if (ws == nullptr || ws_bytes < decode_ws_bytes(*p, cap)) return PUREKV_EWORKSPACE;
-  return launch_decode(*p, q_new, k_new, v_new, kc, vc, n_cached + 1, cap, out, ws, static_cast<hipStream_t>(stream));
-}
-
-int purekv_plan_set_decode_polls(purekv_plan_t* p, int32_t polls) {
-  if (p == nullptr) return PUREKV_EINVAL;
-  p->decode_polls = polls < 0 ? -1 : polls;
-  return PUREKV_OK;
+  return launch_decode(*p, q_new, k_new, v_new, kc, vc, n_cached + 1, cap, out, ws, kDecodeLooks, static_cast<hipStream_t>(stream));
 }
 
 // ---- layer stack: which layer runs which attention, which C drives which layer's selection ----

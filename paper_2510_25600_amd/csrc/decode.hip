@@ -38,7 +38,6 @@ namespace {
 constexpr int DEC_WAVES = 8;     // wavefronts per workgroup
 constexpr int DEC_NT = 64 * DEC_WAVES;
 constexpr int DEC_HB = 16;       // query heads per workgroup
-constexpr int kPolls = 1 << 14;  // looks of a gathering workgroup at partial results before it gives up (0.5 us each)
 
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) shortx4* LdsShortx4;
@@ -58,7 +57,7 @@ struct DecodeArgs {
   float* ws_ml;        // [Hq, max_splits, 2] running maximum (log2 domain) and sum, likewise
   uint64_t* counters;  // [Hkv * head_blocks]: workgroups that have arrived | heads that are gathered << 32, likewise
   int32_t Hq, G, n_cached, cap, n_splits, max_splits, head_blocks;
-  int32_t polls;
+  int32_t looks;       // of a gathering workgroup, before it gives up
   float scale_log2;
 };
 
@@ -118,7 +117,7 @@ __device__ __forceinline__ void count_in(const DecodeArgs& a, int kvh, int hb, i
 
 // Adds up the partial results of head i of the block and writes its output; whole workgroup.  A group of LPR lanes takes the
 // four-column pieces of every NG-th chunk; a wavefront holds the (max, sum) pairs of 64 chunks, one a lane, and turns them
-// into weights with cross-lane steps.  With `counts` it is this workgroup's first gathering: it looks a.polls times at
+// into weights with cross-lane steps.  With `counts` it is this workgroup's first gathering: it looks a.looks times at
 // most, counts itself in and returns what count_in leaves it; without, everything is in memory.
 template <int D, int BYTES>
 __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, int hb, int ng, int i, bool counts,
@@ -136,7 +135,7 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
   const BufferRsrc mlb = make_rsrc(a.ws_ml + (size_t)hq * a.max_splits * 2);
   float run_m = -INFINITY, run_l = 0.f;
   floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-  int polls = counts ? a.polls : kPolls;
+  int looks = counts ? a.looks : kDecodeLooks;
   for (int s0 = 0; s0 < a.n_splits; s0 += 64) {
     const int nsb = min(64, a.n_splits - s0);
     const BufferRsrc ob = make_rsrc(a.ws_o + (size_t)s0 * a.Hq * D);
@@ -154,10 +153,10 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
     for (;;) {
       memory_has_changed();
       load_pairs();
-      if (__popcll(__ballot(pair_there())) >= 64 - nsb / 2 || --polls <= 0) break;
+      if (__popcll(__ballot(pair_there())) >= 64 - nsb / 2 || --looks <= 0) break;
       __builtin_amdgcn_s_sleep(1);
     }
-    while (polls > 0) {
+    while (looks > 0) {
       memory_has_changed();
       load_pairs();
 #pragma unroll
@@ -172,9 +171,9 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
 #pragma unroll
         for (int k = 0; k < 4; ++k) there &= __float_as_uint(ov[u][k]) != 0u;
       if (__all(there)) break;
-      --polls;
+      --looks;
     }
-    if (polls <= 0) break;
+    if (looks <= 0) break;
     const float mnew = fmaxf(run_m, wave_max(ml[0]));
     const float mref = (mnew == -INFINITY) ? 0.f : mnew;   // every score so far is -inf: weights 0, not NaN
     const float f = __builtin_amdgcn_exp2f(ml[0] - mref);
@@ -197,7 +196,7 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
     acc[k] = p.a + p.b;
   }
   if (lane < LPR) *reinterpret_cast<floatx4*>(red + wave * D + 4 * li) = acc;
-  if (lane == 0) failed[wave] = polls <= 0;
+  if (lane == 0) failed[wave] = looks <= 0;
   const float inv = 1.f / run_l;
   __syncthreads();
   int bad = 0;
@@ -515,7 +514,7 @@ int launch_decode_ws_init(void* ws, size_t bytes, hipStream_t st) {
 }
 
 int launch_decode(const purekv_plan& p, const void* q_new, const void* k_new, const void* v_new, void* kc, void* vc,
-                  int32_t n_cached, int32_t cap, void* out, void* ws, hipStream_t st) {
+                  int32_t n_cached, int32_t cap, void* out, void* ws, int32_t looks, hipStream_t st) {
   DecodeArgs a;
   a.q = static_cast<const uint16_t*>(q_new);
   a.k_new = static_cast<const uint16_t*>(k_new);
@@ -527,7 +526,7 @@ int launch_decode(const purekv_plan& p, const void* q_new, const void* k_new, co
   a.head_blocks = decode_head_blocks(p);
   a.n_splits = splits_of(n_cached, tiles);
   a.max_splits = decode_max_splits(p, cap);
-  a.polls = p.decode_polls < 0 ? kPolls : p.decode_polls;
+  a.looks = looks;
   a.counters = static_cast<uint64_t*>(ws);
   a.ws_o = reinterpret_cast<float*>(static_cast<char*>(ws) + decode_counter_bytes(p));
   a.ws_ml = a.ws_o + (size_t)a.max_splits * p.g.Hq * p.g.d;

@@ -134,7 +134,6 @@ struct purekv_plan {
   int32_t n_heads_sel = 0;                 // selected heads (Hq when head_sel is empty)
   int device = -1;
   int n_cu = 256;
-  int32_t decode_polls = -1;               // purekv_plan_set_decode_polls
 };
 
 namespace purekv {

@@ -649,6 +649,21 @@ def test_decode_step_merges_many_chunks(hq, hkv, d, n0):
     check_attention(f64_of(outs[0]), orc.decode_attention(F64(q), F64(kc_h), F64(vc_h)), f"decode {hq}/{hkv} d={d} n={n0 + 1}")
 
 
+MANY = 2 ** 31 - 1   # looks: as many as the library's bound
+
+
+def decode_attn_with_looks(plan, q, kc, vc, n, looks, ws=None):
+    """purekv_decode_attn with a bound of its own on the gathering workgroups' looks (csrc/testing.h).  ws: the workspace to use
+    (default: the plan's)."""
+    nb, cap, out = plan.workspace_bytes(pk.OP_DECODE, cap=kc.shape[-2]), kc.shape[-2], torch.empty_like(q)
+    ws = plan._n.workspace(pk.OP_DECODE, nb, q, 0, 0, cap) if ws is None else ws
+    fn, p = pk.raw().purekv_testing_decode_attn, ctypes.c_void_p
+    fn.argtypes = [p, p, p, p, ctypes.c_int32, ctypes.c_int32, p, p, ctypes.c_size_t, ctypes.c_int32, p]
+    assert fn(plan.handle, q.data_ptr(), kc.data_ptr(), vc.data_ptr(), n, cap, out.data_ptr(), ws.data_ptr(), nb, looks,
+              torch.cuda.current_stream().cuda_stream) == pk.OK
+    return out
+
+
 @pytest.mark.parametrize("hq,hkv,d,ns", [
     (28, 4, 128, (128, 129, 256, 257)),     # one chunk of 128, of 256, the first cut caches
     (28, 4, 128, (57 * 128, 57 * 128 + 1)),  # 256 compute units hold 57 chunks per KV head beside 28 gathering workgroups
@@ -668,10 +683,7 @@ def test_decode_gathers_chunks_of_every_size(hq, hkv, d, ns):
     plan = pk.Plan(1, 4, 4, 4, hq, hkv, d, 3)
     qd, kd, vd = to_dev(q[:, 0]), to_dev(k), to_dev(v)
     for n in ns:
-        outs = []
-        for polls in (-1, 0, -1, 0, 1, -1):
-            plan.set_decode_polls(polls)
-            outs.append(bits_of(pk.purekv_decode_attn(plan, qd, kd, vd, n)))
+        outs = [bits_of(decode_attn_with_looks(plan, qd, kd, vd, n, looks)) for looks in (MANY, 0, MANY, 0, 1, MANY)]
         assert all(np.array_equal(outs[0], o) for o in outs[1:]), f"{hq}/{hkv} n={n}"
         check_attention(f64_of(torch.from_numpy(outs[0].view(np.int16)).view(torch.bfloat16)),
                         orc.decode_attention(F64(q[:, 0]), F64(k[:, :n]), F64(v[:, :n])), f"decode {hq}/{hkv} d={d} n={n}")

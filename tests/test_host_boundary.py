@@ -26,6 +26,15 @@ def test_library_exports_every_declared_symbol():
     assert declared == set(pk.EXPORTS)
 
 
+def test_nothing_changes_a_plan():
+    """A plan may be shared by any number of streams and threads: no declared function takes a plan that is not const, but for
+    the one that destroys it."""
+    header = open(os.path.join(ROOT, "include", "purekv.h")).read()
+    declared = re.findall(r"PUREKV_API[^;(]*?\b(purekv_\w+)\s*\(([^;]*)\);", header)
+    assert len(declared) == len(pk.EXPORTS)
+    assert [name for name, args in declared if re.search(r"(?<!const )purekv_plan_t\*(?!\*)", args)] == ["purekv_plan_destroy"]
+
+
 def test_status_strings():
     for st in (pk.OK, pk.EINVAL, pk.EUNSUPPORTED, pk.EWORKSPACE, pk.EHIP, pk.ENOMEM, -99):
         assert isinstance(pk.purekv_strerror(st), str) and pk.purekv_strerror(st)
