@@ -483,16 +483,22 @@ static size_t decode_counter_bytes(const purekv_plan& p) {
 //   32 on 8 of 128, keys 2500 (192): 7.9, 8.9, 11.8 (9.9); 4000 (288, 160): 9.6, 9.1, 11.7 (10.6); 10000 (352 with two): 18.1, 13.7,
 //   12.7 (17.8);  200 keys, 28 on 4: 6.9, 5.1 (5.1)
 // With more workgroups than compute units the second one of a unit starts its loads behind the first one's.
+// A gathering workgroup takes 64 chunks at a time, each time another round trip or two, so few KV heads are not cut into as many
+// chunks as there is room for: with one tile into 64, with two into 64 with heads of 64, 192 of 128 (four tiles are 147 KB of LDS
+// to fill there).  us, without that limit -> with it (the old kernel): 2 query heads on 1 KV head of 64, 16000 keys 7.6 -> 6.5 (8.0),
+// 31000 11.5 -> 8.0 (10.2), 50000 10.8 -> 9.3 (13.8); 2 on 1 of 128, 16000 9.5 -> 8.4 (9.6), 31000 13.7 -> 10.3 (11.2), 50000 13.7 ->
+// 12.5 (14.2); 4 on 2 of 128, 16000 10.8 -> 9.0 (10.4).  Heads of 128 with two tiles in up to 64 chunks, else four: 18000 keys 10.5
+// instead of 9.6, 33000 12.0 instead of 11.1.
 static int decode_room(const purekv_plan& p) { return (p.n_cu - p.g.Hq) / (p.g.Hkv * decode_head_blocks(p)); }   // chunks per KV head
+static int decode_limit(const purekv_plan& p, int tiles) { return std::min(decode_room(p), tiles == 2 && p.g.d == 128 ? 192 : 64); }
 static int decode_tiles(const purekv_plan& p, int n) {
   if (n <= chunk_keys(1)) return 1;
   if (n <= chunk_keys(2)) return 2;
-  const int room = decode_room(p);
-  return splits_of(n, 1) <= room ? 1 : splits_of(n, 2) <= room ? 2 : 4;
+  return splits_of(n, 1) <= decode_limit(p, 1) ? 1 : splits_of(n, 2) <= decode_limit(p, 2) ? 2 : 4;
 }
 // Chunks of any n <= cap.
 static int decode_max_splits(const purekv_plan& p, int cap) {
-  return std::max({1, std::min(splits_of(cap, 1), decode_room(p)), splits_of(cap, 4)});
+  return std::max({1, std::min(splits_of(cap, 1), decode_limit(p, 1)), std::min(splits_of(cap, 2), decode_limit(p, 2)), splits_of(cap, 4)});
 }
 
 size_t decode_ws_bytes(const purekv_plan& p, int32_t cap) {
