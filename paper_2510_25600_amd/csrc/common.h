@@ -134,8 +134,12 @@ int launch_compact(const purekv_plan& p, const void* k, const void* v, int64_t k
 int launch_append(const purekv_plan& p, const void* k_new, const void* v_new, void* kc, void* vc, int32_t n_cached,
                   int32_t cap, hipStream_t st);
 // k_new, v_new null: attention only; else row n_cached - 1 comes from them and is stored into kc, vc
-// looks: of a gathering workgroup at partial results before it gives up, at most kDecodeLooks
-constexpr int32_t kDecodeLooks = 1 << 14;
+// looks: of a gathering workgroup at partial results before it gives up, at most kDecodeLooks.  It starts when every chunk has a
+// compute unit, so it waits for a chunk's own time: with 64 looks (0.3 to 0.5 us each) no head is given up in caches of 400 to
+// 33000 keys of 1 to 32 KV heads, with 32 some are (16000 keys, 28/4 heads: 12.9 -> 27.5 us).  Four times as many, because the chunks
+// of a call can be held up: by another stream's kernel on one XCD while another XCD's gathering workgroups run.  These keep a
+// compute unit each from that stream meanwhile, 0.1 ms at most; giving up costs 0.4 to 30 us.
+constexpr int32_t kDecodeLooks = 256;
 int launch_decode(const purekv_plan& p, const void* q_new, const void* k_new, const void* v_new, void* kc, void* vc,
                   int32_t n_cached, int32_t cap, void* out, void* ws, int32_t looks, hipStream_t st);
 
