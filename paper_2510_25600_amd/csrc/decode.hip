@@ -197,7 +197,6 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
   }
   if (lane < LPR) *reinterpret_cast<floatx4*>(red + wave * D + 4 * li) = acc;
   if (lane == 0) failed[wave] = looks <= 0;
-  const float inv = 1.f / run_l;
   __syncthreads();
   int bad = 0;
 #pragma unroll
@@ -210,7 +209,7 @@ __device__ __forceinline__ uint32_t gather_head(const DecodeArgs& a, int kvh, in
 #pragma unroll
       for (int wv = 0; wv < DEC_WAVES; ++wv) sum += *reinterpret_cast<const floatx4*>(red + wv * D + 4 * li);
       *reinterpret_cast<u32x2*>(a.out + (size_t)hq * D + 4 * li) =
-          u32x2{pack_bf16(sum[0] * inv, sum[1] * inv), pack_bf16(sum[2] * inv, sum[3] * inv)};
+          u32x2{pack_bf16(sum[0] / run_l, sum[1] / run_l), pack_bf16(sum[2] / run_l, sum[3] / run_l)};
     }
     // nobody reads the partial results again: back to 0
     for (int s0 = 0; s0 < a.n_splits; s0 += 64) {

@@ -689,6 +689,30 @@ def test_decode_gathers_chunks_of_every_size(hq, hkv, d, ns):
                         orc.decode_attention(F64(q[:, 0]), F64(k[:, :n]), F64(v[:, :n])), f"decode {hq}/{hkv} d={d} n={n}")
 
 
+@pytest.mark.parametrize("n", [192, 448, 960, 3904, 8064, 14336])
+def test_decode_divides_by_the_sum(n):
+    """Equal scores and whole-numbered values: sums of probabilities and of values are exact, so an output is the quotient of two whole
+    numbers rounded to fp32 and then to bf16.  Quotients half way between two bf16 numbers (1 + odd / 256) tell a division from a
+    product with the reciprocal, which lands beside the middle."""
+    d, k = 128, n // 64                                    # n = 64 k: the sum of column c is n (1 + (2 c + 1) / 256) = 64 k + k (2 c + 1) / 4
+    v = np.ones((n, d))
+    c = 2 * np.arange(d) + 1
+    extra = (n * c) // 256                                 # the whole part; the rest, in quarters, goes to the last key
+    for j in range(n - 1):
+        take = np.minimum(extra, 127)                      # 1 + 127 = 128: every value has eight significant bits
+        v[j] += take
+        extra = extra - take
+    v[n - 1] += (n * c) % 256 / 256
+    assert not extra.any() and np.array_equal(v.sum(0) * 256, n * (256.0 + c))
+    vt = torch.from_numpy(v[None]).bfloat16()
+    assert np.array_equal(vt.double().numpy()[0], v)
+    plan = pk.Plan(1, 4, 4, 4, 2, 1, d, 3)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    key = torch.randn((1, n, d), generator=gen, device="cuda").bfloat16()
+    out = pk.purekv_decode_attn(plan, torch.zeros((2, d), dtype=torch.bfloat16, device="cuda"), key, vt.cuda(), n)
+    assert torch.equal(out.cpu(), torch.from_numpy(1 + c / 256).bfloat16().expand(2, d))
+
+
 @pytest.mark.parametrize("hq,hkv,d,shorter,longer", [(2, 1, 64, 31000, 33000), (2, 1, 128, 31000, 33000), (4, 2, 128, 16000, 16384)])
 def test_decode_of_a_shorter_cache_takes_no_longer(hq, hkv, d, shorter, longer):
     """Few KV heads are not cut into as many chunks as there are compute units for: a gathering workgroup takes 64 at a time.
