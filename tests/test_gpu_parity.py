@@ -672,21 +672,42 @@ def decode_attn_with_looks(plan, q, kc, vc, n, looks, ws=None):
     (5, 5, 128, (300,)),                    # one query head a KV head: one gathering workgroup each
 ])
 def test_decode_gathers_chunks_of_every_size(hq, hkv, d, ns):
-    """Chunks of 128, 256 and 512 keys, added up by the gathering workgroups or, where these never wait, by the last one: the
-    same bits, against the oracle, three calls each on one workspace (which every call leaves at zero)."""
+    """Chunks of 128, 256 and 512 keys, added up by the gathering workgroups or, where these look once or not at all, by the last
+    one: the same bits, against the oracle.  All on one workspace, with another query and another cache for every length and back:
+    a partial result of an earlier call that was left or read again would be of other numbers.  Every call leaves the
+    workspace at zero, which is what tells a written word, and touches nothing behind it."""
     from workloads import f32_to_bf16_bits
     rng = np.random.default_rng(hq + ns[0])
     cap = max(ns)
-    q, k, v = (f32_to_bf16_bits(rng.standard_normal((x, y, d)).astype(np.float32)) for x, y in ((hq, 1), (hkv, cap), (hkv, cap)))
-    v[:, ::7] = 0    # partial outputs that are exactly zero
-    v[:, :, 5] = 0
     plan = pk.Plan(1, 4, 4, 4, hq, hkv, d, 3)
-    qd, kd, vd = to_dev(q[:, 0]), to_dev(k), to_dev(v)
-    for n in ns:
-        outs = [bits_of(decode_attn_with_looks(plan, qd, kd, vd, n, looks)) for looks in (MANY, 0, MANY, 0, 1, MANY)]
+    nb = plan.workspace_bytes(pk.OP_DECODE, cap=cap)
+    ws = torch.full((nb + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    assert pk.raw().purekv_workspace_init(plan.handle, pk.OP_DECODE, ws.data_ptr(), nb, 0, 0, cap,
+                                          torch.cuda.current_stream().cuda_stream) == pk.OK
+    for n in (*ns, *reversed(ns)):
+        q, k, v = (f32_to_bf16_bits(rng.standard_normal((x, y, d)).astype(np.float32)) for x, y in ((hq, 1), (hkv, cap), (hkv, cap)))
+        v[:, ::7] = 0    # partial outputs that are exactly zero
+        v[:, :, 5] = 0
+        qd, kd, vd = to_dev(q[:, 0]), to_dev(k), to_dev(v)
+        outs = []
+        for looks in (MANY, 0, 1, MANY):
+            outs.append(bits_of(decode_attn_with_looks(plan, qd, kd, vd, n, looks, ws)))
+            assert not ws[:nb].any() and (ws[nb:] == 0xA5).all(), f"{hq}/{hkv} n={n} looks={looks}"
         assert all(np.array_equal(outs[0], o) for o in outs[1:]), f"{hq}/{hkv} n={n}"
         check_attention(f64_of(torch.from_numpy(outs[0].view(np.int16)).view(torch.bfloat16)),
                         orc.decode_attention(F64(q[:, 0]), F64(k[:, :n]), F64(v[:, :n])), f"decode {hq}/{hkv} d={d} n={n}")
+
+
+@pytest.mark.parametrize("hq,hkv,d,n", [(28, 4, 128, 5491), (28, 4, 128, 6900), (16, 2, 64, 4000), (28, 4, 128, 16000)])
+def test_decode_is_gathered_by_the_workgroups_that_wait(hq, hkv, d, n):
+    """Results are the same whoever adds them up, so only the time tells that the gathering workgroups do: the last workgroup alone
+    takes two to three times as long, and looks at registers instead of memory would all be used up first (0.1 ms)."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    plan = pk.Plan(1, 4, 4, 4, hq, hkv, d, 3)
+    q, k, v = (torch.randn(x, generator=gen, device="cuda").bfloat16() for x in ((hq, d), (hkv, n, d), (hkv, n, d)))
+    waits, alone = (_graph_us(lambda: decode_attn_with_looks(plan, q, k, v, n, looks)) for looks in (MANY, 0))
+    print(f"[case] decode {hq}/{hkv} heads of {d}, {n} keys: {waits:.2f} us, {alone:.2f} without waiting", flush=True)
+    assert waits <= 0.75 * alone
 
 
 @pytest.mark.parametrize("n", [192, 448, 960, 3904, 8064, 14336])
