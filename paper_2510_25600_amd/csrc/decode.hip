@@ -19,10 +19,14 @@
 // leaves zeros.  It looks a bounded number of times; one that gives up leaves its head to whoever of the chunks' and the
 // gathering workgroups counts itself in last at the (KV head, head block)'s counter, by when everything is in memory.  So
 // no wait is without end, whatever order the workgroups run in, and only the head that gave up is added up late.
+// What that rests on: a word is stored and loaded whole (a 16-byte piece may arrive in parts, so each of its words is looked at);
+// device-scope (sc1) stores go through to memory, and device-scope loads are not served from an L2's older copy; the zeros that a
+// gathering workgroup leaves are such stores, and a launch on the stream begins when the one before has ended, stores and all.
 // What bounds it is the chain of memory round trips behind the launch.  Counting in and letting the workgroup that arrived
 // last add everything up had four of them behind the chunk's own (stores acknowledged, arrival counted, partial results
 // in, output out) and one compute unit that pulled in all heads of the group; asking for the data itself leaves two and
-// spreads them over as many compute units as there are heads.  5491 keys x 4 KV heads x 7 query heads 9.9 -> 7.6 us a call,
+// spreads them over as many compute units as there are heads.  (Three where a head has more than 48 chunks with heads of 128, 32 of
+// 64: this compiler puts a wait for the others ahead of a lane's last load.)  5491 keys x 4 KV heads x 7 query heads 9.9 -> 7.6 us a call,
 // 6900 keys 11.2 -> 8.8 (28 caches in turn), 1690 keys 8.7 -> 7.0, 10 000 keys x 8 KV heads x 4 17.8 -> 12.5.  (All eight
 // wavefronts asking for pairs and outputs from the start got in the way of the stores they were waiting for: 8.5.  4000
 // keys x 4 x 7, waiting for half of the pairs, all of them, three quarters: 7.64, 7.76, 7.63.)

@@ -52,10 +52,6 @@ __device__ __forceinline__ float row_norm2(float ss) {
   return ss;
 }
 
-// grid = (row blocks, layers * Hkv): a workgroup streams SCORE_ROWS consecutive rows of one (layer, KV head).
-// Rows in flight per lane: four, with twice the workgroups of eight.  One layer of 4608 x 8 rows of 128 5.5 -> 4.7 us, 16384 x 4 6.6 -> 5.8,
-// 8192 x 104 36.0 -> 34.1 (kernel trace).  With two, the last and its compaction together take 73.7 instead of 70.9.
-constexpr int SCORE_UNROLL = 4;
 // Cross-lane primitives on the DPP path of the vector ALU (a few cycles each; the generic shuffles go through
 // the LDS crossbar, ~100 cycles a step with 16 wavefronts on the CU).
 // row_shr:n = 0x110 + n moves a value n lanes up within a row of 16 lanes; row_bcast:15 (0x142) hands lane 15 of
@@ -98,6 +94,10 @@ __device__ __forceinline__ uint32_t wave_scan_max(uint32_t v) {
   return max(v, dpp_move<0x143, 0xc>(0u, v));
 }
 
+// grid = (row blocks, layers * Hkv): a workgroup streams 256 / LPR * SCORE_UNROLL consecutive rows of one (layer, KV head).
+// Rows in flight per lane: four, with twice the workgroups of eight.  One layer of 4608 x 8 rows of 128 5.5 -> 4.7 us, 16384 x 4 6.6 -> 5.8,
+// 8192 x 104 36.0 -> 34.1 (kernel trace).  With two, the last and its compaction together take 73.7 instead of 70.9.
+constexpr int SCORE_UNROLL = 4;
 template <int D>
 __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ c, const uint16_t* __restrict__ v,
                                                     int64_t v_layer_stride, int64_t v_head_stride,
@@ -205,7 +205,9 @@ constexpr uint32_t SEL_LIST = 64;
 constexpr int CROWD = 6;   // of 64 lanes: 64 p^2 share a bin with lane ^ 1 where a fraction p of the keys is in one (12: "three in ten" 0.5 to 1.3 us more)
 // A layer's V of up to 128 KB per KV head (eight loads of 16 bytes per thread, all in flight together) is read by the selecting
 // workgroup itself: one round trip to memory instead of a launch, its drain and the scores' way through memory.  256 keys of 64:
-// 3.8 + 5.1 us in two launches, 4.0 in one.  Beyond that a single CU pulls the rows in slower than the chip does.
+// 3.8 + 5.1 us in two launches, 4.0 in one.  Beyond that a single CU pulls the rows in slower than the chip does: at the line both
+// take the same for few rows (4 KV heads of 128, 512 keys in one launch 6.6 us, 520 in two 6.4), one launch less for many (26 layers
+// of 8 KV heads 9.2, 11.1).
 constexpr int kFusedBytes = 128 * 1024;
 struct ScoreArgs {   // what the scores are formed from: arguments of purekv_topk_select
   const float* c;
