@@ -639,6 +639,19 @@ def _build_module():
     return mod
 
 
+@pytest.mark.parametrize("hq,hkv,d,cap,chunks", [
+    (2, 1, 64, 8192, 64), (2, 1, 64, 31000, 64), (2, 1, 64, 65536, 128),     # one tile up to 64 chunks, two up to 64, four
+    (2, 1, 128, 8192, 64), (2, 1, 128, 31000, 122), (2, 1, 128, 49152, 192), (2, 1, 128, 100000, 196),   # two tiles up to 192
+    (28, 4, 128, 6900, 54), (28, 4, 128, 16000, 57), (32, 32, 128, 33000, 65), (300, 1, 64, 600, 2)])
+def test_decode_workspace_holds_the_chunks_that_any_shorter_cache_is_cut_into(hq, hkv, d, cap, chunks):
+    """256 compute units.  The chunks per KV head are limited by the compute units and, with few KV heads, by what a gathering
+    workgroup takes in few rounds of 64; a workspace for a cache of `cap` keys serves every shorter one."""
+    plan = pk.Plan(1, 4, 4, 4, hq, hkv, d, pk.PATTERN_ST, host_only=True)
+    counters = (hkv * -(-(hq // hkv) // 16) * 8 + 255) // 256 * 256
+    assert plan.workspace_bytes(pk.OP_DECODE, cap=cap) == counters + chunks * hq * (d + 2) * 4
+    plan.close()
+
+
 def test_every_look_at_partial_results_loads_them_again(tmp_path):
     """Decode's gathering workgroups look at memory until other workgroups have written it, with loads that the compiler takes for
     ordinary ones.  In its own intermediate code of every decode kernel, no device-scope load may reach itself without a
